@@ -1,8 +1,8 @@
 // m1_device.h -- device-side building blocks of the M1 step for gfx950:
 // Levermore closure with the Sect. 2.6 signal speeds and the physical flux
 // of one state, the HLL interface flux with the optical-depth limiter, the
-// van Leer and LimO3 slopes and the f-preserving face fix
-// (Eq. f_reconstruct).
+// van Leer and LimO3 slopes and the face treatments (Eq. f_reconstruct and
+// its alternatives).
 // Templated on the working precision R (double or float).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -11,58 +11,55 @@
 
 namespace m1 {
 
-// Arithmetic primitives per precision.  FP64 (arguments are positive normal
-// numbers, or zero for the square root):
-//  * reciprocal: the hardware estimate refined by two Newton steps
-//    r <- r (2 - x r), each doubling the correct bits (within an ulp or two);
-//  * square root: Goldschmidt iteration from the hardware reciprocal square
-//    root y, g = x y and h = y / 2 refined together, then two Newton
-//    corrections g <- g + (x - g^2) h; correctly rounded on every argument
-//    tried from 1e-300 to 1e300, with no range scaling or special-case
-//    handling beyond zero (the callers pass no subnormal or infinite
-//    arguments: squared norms below the smallest normal number are taken
-//    as zero before any reciprocal);
-//  * reciprocal square root: the hardware estimate refined by two Newton
-//    steps y <- y + y (1 - x y^2) / 2.
-// All stay far inside the 1e-12 parity tolerance.  FP32: the hardware
-// reciprocal, square root and reciprocal square root (about 1 ulp), inside
-// 1e-5.
+// Arithmetic primitives per precision.  FP64 refines the hardware estimates
+// (good to 2^-24.4 for the reciprocal and 2^-23.2 for the reciprocal square
+// root, measured) by one step of third order, which leaves 2^-70 and 2^-68 of
+// relative error before rounding in one operation less (reciprocal) and three
+// less (square roots) than two Newton steps, with a shorter chain:
+//  * reciprocal: e = 1 - x r, r <- r (1 + e + e^2);
+//  * reciprocal square root: e = 1 - x y^2, y <- y (1 + e / 2 + 3 e^2 / 8);
+//  * square root: g = x y, h = y / 2, e = 1/2 - h g, g <- g (1 + e + 3 e^2 / 2),
+//    and in sqrt_ one correction g <- g + (x - g^2) h and a select for zero.
+// Arguments are positive normal numbers, or zero for sqrt_ (the callers pass
+// no subnormal or infinite arguments).  All stay within an ulp or two, far
+// inside the 1e-12 parity tolerance.  FP32: the hardware reciprocal, square
+// root and reciprocal square root (about 1 ulp), inside 1e-5.
 template <typename R> struct Num;
 template <> struct Num<double> {
-    // smallest normal number: |F|^2 below it is taken as F = 0, so that the
-    // inverse |F|^-2 stays finite
-    static constexpr double tiny = __DBL_MIN__;
+    static constexpr double tiny = __DBL_MIN__;      // smallest normal number
     static __device__ __forceinline__ double sqrt_(double x)
     {
-        const double y = __builtin_amdgcn_rsq(x);
-        double g = x * y, h = 0.5 * y;
-        const double r = __builtin_fma(-h, g, 0.5);
-        g = __builtin_fma(g, r, g);
-        h = __builtin_fma(h, r, h);
-        double d = __builtin_fma(-g, g, x);
-        g = __builtin_fma(d, h, g);
-        d = __builtin_fma(-g, g, x);
-        g = __builtin_fma(d, h, g);
+        const double y = __builtin_amdgcn_rsq(x), h = 0.5 * y;
+        double g = x * y;
+        const double e = __builtin_fma(-h, g, 0.5);
+        g = __builtin_fma(g, __builtin_fma(1.5 * e, e, e), g);
+        g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
         return x > 0.0 ? g : 0.0;
+    }
+    // x at least the smallest normal number
+    static __device__ __forceinline__ double sqrt_pos(double x)
+    {
+        const double y = __builtin_amdgcn_rsq(x), h = 0.5 * y, g = x * y;
+        const double e = __builtin_fma(-h, g, 0.5);
+        return __builtin_fma(g, __builtin_fma(1.5 * e, e, e), g);
     }
     static __device__ __forceinline__ double rcp(double x)
     {
-        double r = __builtin_amdgcn_rcp(x);
-        r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-        r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-        return r;
+        const double r = __builtin_amdgcn_rcp(x);
+        const double e = __builtin_fma(-x, r, 1.0);
+        return __builtin_fma(r, __builtin_fma(e, e, e), r);
     }
     static __device__ __forceinline__ double rsqrt(double x)
     {
-        double y = __builtin_amdgcn_rsq(x);
-        y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
-        y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
-        return y;
+        const double y = __builtin_amdgcn_rsq(x);
+        const double e = __builtin_fma(-x * y, y, 1.0);
+        return __builtin_fma(y, e * __builtin_fma(0.375, e, 0.5), y);
     }
 };
 template <> struct Num<float> {
     static constexpr float tiny = __FLT_MIN__;
     static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
+    static __device__ __forceinline__ float sqrt_pos(float x) { return __builtin_amdgcn_sqrtf(x); }
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     static __device__ __forceinline__ float rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 };
@@ -89,193 +86,8 @@ __device__ __forceinline__ float vmax(float a, float b) { return __builtin_fmaxf
 __device__ __forceinline__ double vmin(double a, double b) { return __builtin_fmin(a, b); }
 __device__ __forceinline__ double vmax(double a, double b) { return __builtin_fmax(a, b); }
 
-// Closure quantities of one radiation state (E, F) seen from direction d:
-// lambda_-, lambda_+ (Sect. 2.6) and the flux (F_d, E D_{xd}, E D_{yd},
-// E D_{zd}) (Sect. 2.1, Eqs. rad1/rad2), all in units of c_hat.
-template <typename R>
-struct Wave {
-    R lm, lp;
-    R phi[4];
-};
-
-template <typename R, int D>
-__device__ __forceinline__ Wave<R> closure_wave(R E, R Fx, R Fy, R Fz)
-{
-    Wave<R> w;
-    const R F2 = Fx * Fx + Fy * Fy + Fz * Fz;
-    const R Fn = F2 >= Num<R>::tiny ? Num<R>::sqrt_(F2) : R(0);    // F = 0 below the normal range
-    R f = Fn / E;
-    f = f > R(1) ? R(1) : f;
-    const R f2 = f * f;
-    const R s = Num<R>::sqrt_(R(4) - R(3) * f2);
-    const R xi = (R(3) + R(4) * f2) / (R(5) + R(2) * s);
-    const R Fd = D == 0 ? Fx : (D == 1 ? Fy : Fz);
-    // n = F / |F| (n = 0 for F = 0)
-    const R inv = Fn > R(0) ? R(1) / Fn : R(0);
-    const R mu = Fd * inv;
-    R z2 = (R(2) / R(3)) * (R(4) - R(3) * f2 - s) + R(2) * mu * mu * (R(2) - f2 - s);
-    z2 = z2 < R(0) ? R(0) : z2;
-    const R zeta = Num<R>::sqrt_(z2);
-    const R a = (f * mu - zeta) / s, b = (f * mu + zeta) / s;
-    w.lm = a < b ? a : b;
-    w.lp = a < b ? b : a;
-    const R iso = R(0.5) * (R(1) - xi) * E;
-    const R an = R(0.5) * (R(3) * xi - R(1)) * E;
-    const R nd = mu;
-    w.phi[0] = Fd;
-    w.phi[1] = an * (Fx * inv) * nd + (D == 0 ? iso : R(0));
-    w.phi[2] = an * (Fy * inv) * nd + (D == 1 ? iso : R(0));
-    w.phi[3] = an * (Fz * inv) * nd + (D == 2 ? iso : R(0));
-    return w;
-}
-
-// HLL flux c_hat * Phi* between face states UL | UR (Sect. 2.5) with the
-// speeds lambda_L = min lambda_-, lambda_R = max lambda_+ clamped to
-// -+4/(3 tau) for tau > 0 (Sect. 2.6), S_L = min(lambda_L, 0),
-// S_R = max(lambda_R, 0); S_L = S_R = 0 falls back to the average flux.
-template <typename R, int D>
-__device__ __forceinline__ void hll_flux(const R UL[4], const R UR[4], R tau, R c_hat, R out[4],
-                                         int riemann = M1_RIEMANN_HLL)
-{
-    const Wave<R> wl = closure_wave<R, D>(UL[0], UL[1], UL[2], UL[3]);
-    const Wave<R> wr = closure_wave<R, D>(UR[0], UR[1], UR[2], UR[3]);
-    R lamL = wl.lm < wr.lm ? wl.lm : wr.lm;
-    R lamR = wl.lp > wr.lp ? wl.lp : wr.lp;
-    if (tau > R(0)) {
-        const R lim = R(4) / (R(3) * tau);
-        lamL = lamL < -lim ? -lim : lamL;
-        lamR = lamR > lim ? lim : lamR;
-    }
-    if (riemann == M1_RIEMANN_LF) {
-        const R aL = lamL < R(0) ? -lamL : lamL, aR = lamR < R(0) ? -lamR : lamR;
-        const R sp = aL > aR ? aL : aR;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = c_hat * (R(0.5) * (wl.phi[q] + wr.phi[q]) - R(0.5) * sp * (UR[q] - UL[q]));
-        return;
-    }
-    const R SL = lamL < R(0) ? lamL : R(0);
-    const R SR = lamR > R(0) ? lamR : R(0);
-    if (SR > SL) {
-        const R k = c_hat / (SR - SL);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            out[q] = k * (SR * wl.phi[q] - SL * wr.phi[q] + SL * SR * (UR[q] - UL[q]));
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = c_hat * R(0.5) * (wl.phi[q] + wr.phi[q]);
-    }
-}
-
-// van Leer limited slope of divided differences (harmonic mean, 0 at extrema).
-template <typename R>
-__device__ __forceinline__ R vanleer(R dl, R dr)
-{
-    const R p = dl * dr;
-    return p > R(0) ? (R(2) * p) / (dl + dr) : R(0);
-}
-
-// f-preserving fix of a reconstructed face state against its donor cell
-// centre (Eq. f_reconstruct): keep F_face iff f_face <= 1 and f_face >
-// f_centre, else F_face = F_centre * E_face / E_centre; E_face <= 0 falls back
-// to the centre state.
-template <typename R>
-__device__ __forceinline__ void ffix(R U[4], const R C[4])
-{
-    if (U[0] > R(0)) {
-        const R ff = Num<R>::sqrt_(U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) / U[0];
-        const R fc = Num<R>::sqrt_(C[1] * C[1] + C[2] * C[2] + C[3] * C[3]) / C[0];
-        if (!(ff <= R(1) && ff > fc)) {
-            const R r = U[0] / C[0];
-            U[1] = C[1] * r;
-            U[2] = C[2] * r;
-            U[3] = C[3] * r;
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) U[q] = C[q];
-    }
-}
-
-
-// ---------------------------------------------------------------------------
-// Face-flux building blocks with a run-time direction (used by the tiled
-// kernel, where one wavefront mixes x and y faces).  Same mathematics as
-// closure_wave / hll_flux / ffix, arranged to need four reciprocals and two
-// square roots per state: with E^-1, |F|^-2 and s = sqrt(4 - 3 f^2) (in
-// FP64 s and 1 / s come from one refined reciprocal square root instead,
-// s = (4 - 3 f^2) / sqrt(4 - 3 f^2): eight FP64 operations fewer; in FP32
-// that form, one transcendental fewer, raised the 100-step deviation of the
-// flux from the FP64 form by a quarter, so FP32 keeps the hardware square
-// root and reciprocal),
-//   f mu = F_d / E (unclamped f) or F_d / |F| (f clamped to 1),
-//   n_i n_d = F_i F_d / |F|^2,  lambda_-+ = (f mu -+ zeta) / s.
-// ---------------------------------------------------------------------------
-
-template <typename R>
-__device__ __forceinline__ Wave<R> closure_wave_rt(R E, R Fx, R Fy, R Fz, int d)
-{
-    Wave<R> w;
-    const R F2 = Fx * Fx + Fy * Fy + Fz * Fz;
-    const R iE = Num<R>::rcp(E);
-    R f2 = F2 * iE * iE;
-    const bool clamped = f2 > R(1);
-    f2 = vmin(f2, R(1));
-    const R s2 = R(4) - R(3) * f2;                 // in [1, 4]
-    R s, is64 = R(0);
-    if constexpr (sizeof(R) == 8) {
-        is64 = Num<R>::rsqrt(s2);
-        s = s2 * is64;
-    } else {
-        s = Num<R>::sqrt_(s2);
-    }
-    // Levermore: xi = (3 + 4 f^2) / (5 + 2 s) = (5 - 2 s) / 3, so
-    // (1 - xi) / 2 = (s - 1) / 3 and (3 xi - 1) / 2 = 2 - s
-    // |F|^2 under the smallest normal number counts as F = 0: its inverse
-    // square would overflow, and a far-field flux that small (the numerical
-    // tail ahead of a front) carries no direction worth resolving
-    const R iFn = F2 >= Num<R>::tiny ? Num<R>::rsqrt(F2) : R(0);
-    const R iF2 = iFn * iFn;
-    const R Fd = d == 0 ? Fx : (d == 1 ? Fy : Fz);
-    const R mu2 = Fd * Fd * iF2;
-    const R z2 = vmax((R(2) / R(3)) * (R(4) - R(3) * f2 - s) + R(2) * mu2 * (R(2) - f2 - s), R(0));
-    const R zeta = Num<R>::sqrt_(z2);
-    const R fmu = Fd * (clamped ? iFn : iE);
-    const R is = sizeof(R) == 8 ? is64 : Num<R>::rcp(s);
-    w.lm = (fmu - zeta) * is;
-    w.lp = (fmu + zeta) * is;
-    const R iso = (s - R(1)) * (R(1) / R(3)) * E;
-    const R c = (R(2) - s) * E * iF2 * Fd;
-    w.phi[0] = Fd;
-    w.phi[1] = c * Fx + (d == 0 ? iso : R(0));
-    w.phi[2] = c * Fy + (d == 1 ? iso : R(0));
-    w.phi[3] = c * Fz + (d == 2 ? iso : R(0));
-    return w;
-}
-
-// f-preserving fix with squared norms: with r = E_f / E_c, keep F_face iff
-// |F_f|^2 <= E_f^2 and |F_f|^2 > |F_c|^2 r^2 (E > 0), i.e. f_face <= 1 and
-// f_face > f_centre; otherwise F_face = r F_centre.
-template <typename R>
-__device__ __forceinline__ void ffix_sq(R U[4], const R C[4])
-{
-    if (U[0] > R(0)) {
-        const R Ff2 = U[1] * U[1] + U[2] * U[2] + U[3] * U[3];
-        const R Fc2 = C[1] * C[1] + C[2] * C[2] + C[3] * C[3];
-        const R r = U[0] * Num<R>::rcp(C[0]);
-        const bool keep = Ff2 <= U[0] * U[0] && Ff2 > Fc2 * (r * r);
-        if (!keep) {
-            U[1] = C[1] * r;
-            U[2] = C[2] * r;
-            U[3] = C[3] * r;
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) U[q] = C[q];
-    }
-}
-
-// Donor-cell quantities of the f-preserving fix, |F_c|^2 and 1 / E_c,
-// computed once per cell and plane for all the faces the cell feeds.
+// Donor-cell quantities of the f-preserving fix, f_c^2 = |F_c|^2 / E_c^2 and
+// 1 / E_c, computed once per cell and plane for all the faces the cell feeds.
 template <typename R>
 struct Centre {
     R f2, ie;
@@ -283,48 +95,174 @@ struct Centre {
 template <typename R>
 __device__ __forceinline__ Centre<R> centre_of(const R C[4])
 {
-    return {C[1] * C[1] + C[2] * C[2] + C[3] * C[3], Num<R>::rcp(C[0])};
+    const R ie = Num<R>::rcp(C[0]);
+    return {(C[1] * C[1] + C[2] * C[2] + C[3] * C[3]) * ie * ie, ie};
 }
 
-// ffix_sq with the donor cell's quantities supplied
-// (E_face <= 0 falls back to the centre state: ratio 1 and E_face = E_c).
+// A face state after its face treatment, with the two quantities the
+// treatment and the closure share: f^2 = |F|^2 / E^2 (not clamped) and 1 / E.
 template <typename R>
-__device__ __forceinline__ void ffix_sq_c(R U[4], const R C[4], Centre<R> cc)
+struct Face {
+    R E, F[3], f2, ie;
+};
+
+// f-preserving fix of a reconstructed face state U against its donor cell C
+// (Eq. f_reconstruct): keep F_face iff f_face <= 1 and f_face > f_centre,
+// else F_face = F_c E_f / E_c; E_face <= 0 falls back to the centre state.
+// The comparison is made on f^2, which the closure needs in either case (the
+// rescaled state has the centre's), so it costs no operation of its own.
+template <typename R>
+__device__ __forceinline__ Face<R> ffix(const R U[4], const R C[4], Centre<R> cc)
 {
+    Face<R> s;
     const bool pos = U[0] > R(0);
-    const R Ff2 = U[1] * U[1] + U[2] * U[2] + U[3] * U[3];
-    const R r = pos ? U[0] * cc.ie : R(1);
-    const bool keep = pos && Ff2 <= U[0] * U[0] && Ff2 > cc.f2 * (r * r);
-    if (!keep) {
-        U[1] = C[1] * r;
-        U[2] = C[2] * r;
-        U[3] = C[3] * r;
+    s.E = pos ? U[0] : C[0];
+    s.ie = Num<R>::rcp(s.E);
+    s.f2 = (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) * s.ie * s.ie;
+    s.F[0] = U[1];
+    s.F[1] = U[2];
+    s.F[2] = U[3];
+    if (!(pos && s.f2 <= R(1) && s.f2 > cc.f2)) {
+        const R r = s.E * cc.ie;
+        s.F[0] = C[1] * r;
+        s.F[1] = C[2] * r;
+        s.F[2] = C[3] * r;
+        s.f2 = cc.f2;
     }
-    U[0] = pos ? U[0] : C[0];
+    return s;
 }
 
-// Face treatment selected at run time: the f-preserving fix (default), the
-// "PLUTO" flat fallback or the simple clip (the alternatives of Sect. 2.5 and
-// the beam comparison of Sect. 3.2); both alternatives act only when
-// |R(F)| > R(E) and fall back to the flat state for R(E) <= 0.
+// The other face treatments, selected at run time: the "PLUTO" flat fallback
+// or the simple clip (the alternatives of Sect. 2.5 and the beam comparison
+// of Sect. 3.2); both act only when |R(F)| > R(E) and fall back to the flat
+// state for R(E) <= 0.
 template <typename R>
-__device__ __forceinline__ void face_fix(int recon, R U[4], const R C[4])
+__device__ __forceinline__ Face<R> face_fix(int recon, const R U[4], const R C[4])
 {
-    if (recon == M1_RECON_FPRESERVE) {
-        ffix_sq(U, C);
-        return;
-    }
+    R V[4] = {U[0], U[1], U[2], U[3]};
     const R Ff2 = U[1] * U[1] + U[2] * U[2] + U[3] * U[3];
-    if (U[0] > R(0) && Ff2 <= U[0] * U[0]) return;
-    if (recon == M1_RECON_CLIP && U[0] > R(0)) {
-        const R sc = U[0] * Num<R>::rcp(Num<R>::sqrt_(Ff2));
-        U[1] *= sc;
-        U[2] *= sc;
-        U[3] *= sc;
-        return;
-    }
+    if (!(U[0] > R(0) && Ff2 <= U[0] * U[0])) {
+        if (recon == M1_RECON_CLIP && U[0] > R(0)) {
+            const R sc = U[0] * Num<R>::rsqrt(Ff2);
+            V[1] *= sc;
+            V[2] *= sc;
+            V[3] *= sc;
+        } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) U[q] = C[q];
+            for (int q = 0; q < 4; ++q) V[q] = C[q];
+        }
+    }
+    const R ie = Num<R>::rcp(V[0]);
+    return {V[0], {V[1], V[2], V[3]}, (V[1] * V[1] + V[2] * V[2] + V[3] * V[3]) * ie * ie, ie};
+}
+
+// component of (x, y, z) along d, by value (a conditional between members
+// would select an address and keep the state in memory)
+template <typename R>
+__device__ __forceinline__ R along(int d, R x, R y, R z)
+{
+    return d == 0 ? x : (d == 1 ? y : z);
+}
+
+// Closure of a face state seen from direction d (Sect. 2.1, 2.6), all in units
+// of c_hat: signal speeds lm <= lp and the flux as
+//   Phi_0 = F_d,  Phi_q = c F_q + (q = d) iso.
+// With s = sqrt(4 - 3 f^2) Levermore's xi is (5 - 2 s) / 3, so that
+// (1 - xi) / 2 = (s - 1) / 3 and (3 xi - 1) / 2 = 2 - s.  2 - s vanishes with
+// f^2, as 3 f^2 / (2 + s), which takes 1 / |F|^2 out of every expression: with
+// phi = F_d / E and m = phi / (2 + s),
+//   c      = (2 - s) E F_d / |F|^2        = 3 m,
+//   zeta^2 = 2 (s - 1) (s / 3 - phi m)     (lambda_-+ = (phi -+ zeta) / s).
+// No direction n = F / |F| is formed, so F = 0 and fluxes whose square is
+// below the normal range need no case of their own, and the difference 2 - s
+// of nearly equal numbers at small f is gone.  f > 1 (a centre state past the
+// limit by a rounding, or a caller's) counts as f = 1: s = 1, phi = F_d / |F|
+// and c = E F_d / |F|^2, a branch that no wavefront usually takes.
+// FP64 takes s and 1 / s from one reciprocal square root; FP32 the hardware
+// square root and reciprocal (the rsqrt form is two operations shorter, but
+// raised the 100-step deviation of the flux from the FP64 form by a quarter).
+template <typename R>
+struct Wave {
+    R lm, lp, c, iso;
+};
+
+template <typename R>
+__device__ __forceinline__ void limit_f(Face<R> &u, R &k)
+{
+    const R y = u.f2 > R(1) ? Num<R>::rsqrt(u.f2) : R(1);
+    u.ie *= y;
+    k *= y;
+    u.f2 = vmin(u.f2, R(1));
+}
+
+template <typename R>
+__device__ __forceinline__ Wave<R> closure_of(const Face<R> &u, int d, R k)
+{
+    Wave<R> w;
+    const R phi = along(d, u.F[0], u.F[1], u.F[2]) * u.ie;
+    const R s2 = R(4) - R(3) * u.f2;               // in [1, 4]
+    R s, is;
+    if constexpr (sizeof(R) == 8) {
+        is = Num<R>::rsqrt(s2);
+        s = s2 * is;
+    } else {
+        s = Num<R>::sqrt_(s2);
+        is = Num<R>::rcp(s);
+    }
+    const R m = phi * Num<R>::rcp(R(2) + s);
+    const R g = s - R(1);
+    // the lower bound keeps the FP64 square root's argument normal
+    const R zeta = Num<R>::sqrt_pos(vmax((g + g) * (R(1.0 / 3.0) * s - phi * m), Num<R>::tiny));
+    w.lm = (phi - zeta) * is;
+    w.lp = (phi + zeta) * is;
+    w.c = k * m;
+    w.iso = g * (R(1.0 / 3.0) * u.E);
+    return w;
+}
+
+// Interface flux c_hat Phi* between two face states L | R (Sect. 2.5): HLL
+// with lambda_L = min lambda_-, lambda_R = max lambda_+ clamped to -+4/(3 tau)
+// (Sect. 2.6), S_L = min(lambda_L, 0), S_R = max(lambda_R, 0), the average flux
+// for S_L = S_R = 0; or Lax-Friedrichs-Rusanov, which is HLL with S_R = -S_L
+// the largest limited speed magnitude.  With k = c_hat / (S_R - S_L),
+// a = k S_R and b = -k S_L,
+//   k (S_R Phi_L - S_L Phi_R + S_L S_R (U_R - U_L))
+//     = a (c_L - S_L) F_L + b (c_R - S_R) F_R + (q = d) (a iso_L + b iso_R)
+// for the flux components (two operations each instead of five), and for the
+// energy a F_Ld + b F_Rd + a S_L (E_R - E_L), where the difference is kept: at
+// small f its rounding must go with E_R - E_L, not with E.
+// tau_sum is the sum of the two cells' optical depths: 4 / (3 tau) is
+// 8 / (3 tau_sum), and as |lambda| <= 1 the limit is without effect for
+// tau_sum below 1, which keeps the reciprocal finite at tau = 0.
+template <typename R>
+__device__ __forceinline__ void interface_flux(int d, Face<R> l, Face<R> r, R tau_sum, R c_hat,
+                                               R out[4], int riemann)
+{
+    R kl = R(3), kr = R(3);
+    if (vmax(l.f2, r.f2) > R(1)) {
+        limit_f(l, kl);
+        limit_f(r, kr);
+    }
+    const Wave<R> wl = closure_of(l, d, kl), wr = closure_of(r, d, kr);
+    const R lim = R(8.0 / 3.0) * Num<R>::rcp(vmax(tau_sum, R(1)));
+    R SL = vmax(vmin(vmin(wl.lm, wr.lm), R(0)), -lim);
+    R SR = vmin(vmax(vmax(wl.lp, wr.lp), R(0)), lim);
+    R a = R(0.5) * c_hat, b = a;
+    if (riemann == M1_RIEMANN_LF) {
+        const R lamL = vmax(vmin(wl.lm, wr.lm), -lim), lamR = vmin(vmax(wl.lp, wr.lp), lim);
+        SR = vmax(__builtin_fabs(lamL), __builtin_fabs(lamR));
+        SL = -SR;
+    } else if (SR > SL) {
+        const R k = c_hat * Num<R>::rcp(SR - SL);
+        a = k * SR;
+        b = -(k * SL);
+    }
+    const R el = a * (wl.c - SL), er = b * (wr.c - SR);
+    const R iso = a * wl.iso + b * wr.iso;
+    const R Fl = along(d, l.F[0], l.F[1], l.F[2]), Fr = along(d, r.F[0], r.F[1], r.F[2]);
+    out[0] = (a * SL) * (r.E - l.E) + (a * Fl + b * Fr);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) out[1 + q] = el * l.F[q] + (er * r.F[q] + (d == q ? iso : R(0)));
 }
 
 // the hardware's legacy multiply, 0 x anything = 0 (through the compiler's
@@ -354,14 +292,13 @@ __device__ __forceinline__ double vanleer_fast<double>(double dl, double dr)
     return den >= Num<double>::tiny ? num * Num<double>::rcp(den) : 0.0;
 }
 
-// HLL flux c_hat Phi* at the face between donor cells b (left) and c (right)
-// along d from their states, van Leer slopes (sb, sc; per unit length) and
-// f-fix quantities (cb, cc):
-// face states q_b + s_b hp_b and q_c - s_c hm_c, the face fix, both
-// closures and the optical-depth-limited HLL (or LF) flux.
+// Flux at the face between donor cells b (left) and c (right) along d from
+// their states, slopes (sb, sc; per unit length) and f-fix quantities (cb,
+// cc): face states q_b + s_b hp_b and q_c - s_c hm_c, the face treatment, both
+// closures and the optical-depth-limited flux.
 template <typename R>
 __device__ __forceinline__ void face_flux_s(int d, const R qb[4], const R qc[4], const R sb[4], const R sc[4],
-                                            Centre<R> cb, Centre<R> cc, R hpL, R hmR, R tauL, R tauR, R c_hat,
+                                            Centre<R> cb, Centre<R> cc, R hpL, R hmR, R tau_sum, R c_hat,
                                             R out[4], int recon = M1_RECON_FPRESERVE,
                                             int riemann = M1_RIEMANN_HLL)
 {
@@ -371,38 +308,15 @@ __device__ __forceinline__ void face_flux_s(int d, const R qb[4], const R qc[4],
         UL[v] = qb[v] + sb[v] * hpL;
         UR[v] = qc[v] - sc[v] * hmR;
     }
+    Face<R> l, r;
     if (recon == M1_RECON_FPRESERVE) {
-        ffix_sq_c(UL, qb, cb);
-        ffix_sq_c(UR, qc, cc);
+        l = ffix(UL, qb, cb);
+        r = ffix(UR, qc, cc);
     } else {
-        face_fix(recon, UL, qb);
-        face_fix(recon, UR, qc);
+        l = face_fix(recon, UL, qb);
+        r = face_fix(recon, UR, qc);
     }
-    const Wave<R> wl = closure_wave_rt(UL[0], UL[1], UL[2], UL[3], d);
-    const Wave<R> wr = closure_wave_rt(UR[0], UR[1], UR[2], UR[3], d);
-    const R tau = R(0.5) * (tauL + tauR);
-    // optical-depth limit 4 / (3 tau) (none for tau = 0, or below the
-    // normal range)
-    const R lim = tau >= Num<R>::tiny ? R(4) / R(3) * Num<R>::rcp(tau) : R(__builtin_inf());
-    const R lamL = vmax(vmin(wl.lm, wr.lm), -lim);
-    const R lamR = vmin(vmax(wl.lp, wr.lp), lim);
-    if (riemann == M1_RIEMANN_LF) {
-        // Lax-Friedrichs-Rusanov: largest limited speed magnitude
-        const R sp = vmax(__builtin_fabs(lamL), __builtin_fabs(lamR));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = c_hat * (R(0.5) * (wl.phi[q] + wr.phi[q]) - R(0.5) * sp * (UR[q] - UL[q]));
-        return;
-    }
-    const R SL = vmin(lamL, R(0));
-    const R SR = vmax(lamR, R(0));
-    if (SR > SL) {
-        const R k = c_hat * Num<R>::rcp(SR - SL);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = k * (SR * wl.phi[q] - SL * wr.phi[q] + SL * SR * (UR[q] - UL[q]));
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = c_hat * R(0.5) * (wl.phi[q] + wr.phi[q]);
-    }
+    interface_flux(d, l, r, tau_sum, c_hat, out, riemann);
 }
 
 // van Leer slopes of the four fields of cell m from cells m-1, m, m+1 and the

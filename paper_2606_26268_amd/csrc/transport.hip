@@ -118,7 +118,7 @@ __device__ __forceinline__ R face_diff(R al, R ah, R flo, R fhi)
 // A_hi/V * Phi_hi - A_lo/V * Phi_lo to acc.
 template <typename R, int D, int GEOM>
 __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int stride, int t,
-                                              R tr, R acc[4])
+                                              R tr, Centre<R> c0, R acc[4])
 {
     const int n = a.n[D], lo = a.bc[D][0], hi = a.bc[D][1];
     R q[5][4];
@@ -130,8 +130,9 @@ __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int s
         if (a.special) ghost_fix(a, D, t - 2 + s, n, q[s]);
     }
     const R *winv = a.m.winv[D], *hp = a.m.hp[D], *hm = a.m.hm[D];
-    // face states: cell t-1 upper, cell t lower and upper, cell t+1 lower
-    R Lm[4], Rt[4], Lt[4], Rp[4];
+    // slopes: cell t-1 for its upper face, cell t for its lower and upper
+    // faces, cell t+1 for its lower face
+    R sm[4], slo[4], shi[4], sp[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const R dA = (q[1][v] - q[0][v]) * winv[t + 1];
@@ -141,45 +142,37 @@ __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int s
         if (a.limo3) {
             // each face takes its own slope: the difference on the face side
             // is the near one
-            Lm[v] = q[1][v] + limo3(dA, dB) * hp[t + 1];
-            Rt[v] = q[2][v] - limo3(dC, dB) * hm[t + 2];
-            Lt[v] = q[2][v] + limo3(dB, dC) * hp[t + 2];
-            Rp[v] = q[3][v] - limo3(dD, dC) * hm[t + 3];
+            sm[v] = limo3(dA, dB);
+            slo[v] = limo3(dC, dB);
+            shi[v] = limo3(dB, dC);
+            sp[v] = limo3(dD, dC);
         } else {
-            const R sm = vanleer(dA, dB), s0 = vanleer(dB, dC), sp = vanleer(dC, dD);
-            Lm[v] = q[1][v] + sm * hp[t + 1];
-            Rt[v] = q[2][v] - s0 * hm[t + 2];
-            Lt[v] = q[2][v] + s0 * hp[t + 2];
-            Rp[v] = q[3][v] - sp * hm[t + 3];
+            sm[v] = vanleer_fast(dA, dB);
+            slo[v] = shi[v] = vanleer_fast(dB, dC);
+            sp[v] = vanleer_fast(dC, dD);
         }
     }
-    if (a.recon == M1_RECON_FPRESERVE) {
-        ffix(Lm, q[1]);
-        ffix(Rt, q[2]);
-        ffix(Lt, q[2]);
-        ffix(Rp, q[3]);
-    } else {
-        face_fix(a.recon, Lm, q[1]);
-        face_fix(a.recon, Rt, q[2]);
-        face_fix(a.recon, Lt, q[2]);
-        face_fix(a.recon, Rp, q[3]);
-    }
     const R tm = a.tau[li[1]], t0 = a.tau[li[2]], tp = a.tau[li[3]];
+    const Centre<R> cm = centre_of(q[1]), cp = centre_of(q[3]);
     R flo[4], fhi[4];
-    hll_flux<R, D>(Lm, Rt, R(0.5) * (tm + t0), a.c_hat, flo, a.riemann);
-    hll_flux<R, D>(Lt, Rp, R(0.5) * (t0 + tp), a.c_hat, fhi, a.riemann);
+    face_flux_s<R>(D, q[1], q[2], sm, slo, cm, c0, hp[t + 1], hm[t + 2], tm + t0, a.c_hat, flo, a.recon, a.riemann);
+    face_flux_s<R>(D, q[2], q[3], shi, sp, c0, cp, hp[t + 2], hm[t + 3], t0 + tp, a.c_hat, fhi, a.recon, a.riemann);
     const R al = a.m.alo[D][t] * tr, ah = a.m.ahi[D][t] * tr;
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] += face_diff<same_area<GEOM, D>>(al, ah, flo[v], fhi[v]);
 }
 
 template <typename R, int D>
-__device__ __forceinline__ void ignorable_div(const TArgs<R> &a, const R U[4], R tr, R acc[4])
+__device__ __forceinline__ void ignorable_div(const TArgs<R> &a, const R U[4], Centre<R> c0, R tr, R acc[4])
 {
-    const Wave<R> w = closure_wave<R, D>(U[0], U[1], U[2], U[3]);
+    Face<R> u{U[0], {U[1], U[2], U[3]}, c0.f2, c0.ie};
+    R k = R(3);
+    limit_f(u, k);
+    const Wave<R> w = closure_of(u, D, k);
     const R dA = (a.m.ahi[D][0] - a.m.alo[D][0]) * tr * a.c_hat;
+    acc[0] += dA * U[1 + D];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] += dA * w.phi[v];
+    for (int q = 0; q < 3; ++q) acc[1 + q] += dA * (w.c * U[1 + q] + (q == D ? w.iso : R(0)));
 }
 
 // U* = U - dt div(Phi) + dt c_hat S_geo(U), then E >= floor and f <= 1
@@ -194,14 +187,14 @@ __device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Cen
 
     if (GEOM != M1_CARTESIAN) {
         // geometric sources from the cell-centre pressure tensor
-        // P_ij = (2 - s) E F_i F_j / |F|^2 + delta_ij (s - 1) E / 3 (Levermore:
-        // (3 xi - 1) / 2 = 2 - s, (1 - xi) / 2 = (s - 1) / 3), from the cell's
-        // |F|^2 and 1 / E
-        const R f2 = vmin(cu.f2 * cu.ie * cu.ie, R(1));
-        const R s = Num<R>::sqrt_(R(4) - R(3) * f2);
-        const R iF2 = cu.f2 >= Num<R>::tiny ? Num<R>::rcp(cu.f2) : R(0);
+        // P_ij = an F_i F_j + delta_ij iso, an = (2 - s) E / |F|^2
+        // = 3 / ((2 + s) E) and iso = (s - 1) E / 3 (closure_of), from the
+        // cell's f^2 and 1 / E; f > 1 counts as f = 1
+        const R f2 = vmin(cu.f2, R(1));
+        const R s = Num<R>::sqrt_pos(R(4) - R(3) * f2);
+        R an = R(3) * cu.ie * Num<R>::rcp(R(2) + s);
+        if (cu.f2 > R(1)) an *= Num<R>::rcp(cu.f2);
         const R iso = (s - R(1)) * (R(1) / R(3)) * U[0];
-        const R an = (R(2) - s) * U[0] * iF2;
         const R k_ = a.dt * a.c_hat * ir;
         if (GEOM == M1_CYLINDRICAL) {           // (R, phi, z)
             const R Ppp = an * U[2] * U[2] + iso, PRp = an * U[1] * U[2];
@@ -220,15 +213,21 @@ __device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Cen
     const bool floored = Us[0] < a.e_floor;
     if (floored) Us[0] = a.e_floor;
     count_hits(a.cnt, 0, floored);
-    const R Fn = Num<R>::sqrt_(Us[1] * Us[1] + Us[2] * Us[2] + Us[3] * Us[3]);
-    const bool clipped = Fn > Us[0];
-    if (clipped) {
-        const R sc = Us[0] * Num<R>::rcp(Fn);
-        Us[1] *= sc;
-        Us[2] *= sc;
-        Us[3] *= sc;
+    // |F| > E is rare: its square root and reciprocal are left to wavefronts
+    // with a cell near or past the limit (the margin covers the rounding of
+    // the squares, the comparison itself is that of |F| with E)
+    const R F2 = Us[1] * Us[1] + Us[2] * Us[2] + Us[3] * Us[3];
+    if (!(F2 < R(0.9999) * Us[0] * Us[0])) {
+        const R Fn = Num<R>::sqrt_(F2);
+        const bool clipped = Fn > Us[0];
+        if (clipped) {
+            const R sc = Us[0] * Num<R>::rcp(Fn);
+            Us[1] *= sc;
+            Us[2] *= sc;
+            Us[3] *= sc;
+        }
+        count_hits(a.cnt, 1, clipped);
     }
-    count_hits(a.cnt, 1, clipped);
 #pragma unroll
     for (int v = 0; v < 4; ++v) a.out[v][id] = Us[v];
 }
@@ -237,30 +236,25 @@ template <typename R, int NDIM, int GEOM>
 __global__ void __launch_bounds__(256) k_transport(TArgs<R> a)
 {
     select_group(a);
-    const int n0 = a.n[0], n1 = a.n[1], n2 = a.n[2];
-    const int N = n0 * n1 * n2;
+    const int n0 = a.n[0], n1 = a.n[1];
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= N) return;
-    const int i = id % n0, j = (id / n0) % n1, k = id / (n0 * n1);
+    if (id >= n0 * n1) return;
+    const int i = id % n0, j = id / n0;
     R U[4];
     load4(a, id, U);
     R acc[4] = {R(0), R(0), R(0), R(0)};
+    const Centre<R> c0 = centre_of(U);
 
-    direction_div<R, 0, GEOM>(a, id - i, 1, i, R(1), acc);
+    direction_div<R, 0, GEOM>(a, id - i, 1, i, R(1), c0, acc);
     if (NDIM >= 2) {
         const R tr = a.m.trA[1][i];
-        direction_div<R, 1, GEOM>(a, id - j * n0, n0, j, tr, acc);
+        direction_div<R, 1, GEOM>(a, id - j * n0, n0, j, tr, c0, acc);
     } else if (a.ign[1]) {
-        ignorable_div<R, 1>(a, U, a.m.trA[1][i], acc);
+        ignorable_div<R, 1>(a, U, c0, a.m.trA[1][i], acc);
     }
-    if (NDIM >= 3) {
-        const R tr = a.m.trA[2][i] * a.m.trB[2][j];
-        direction_div<R, 2, GEOM>(a, id - k * n0 * n1, n0 * n1, k, tr, acc);
-    } else if (a.ign[2]) {
-        ignorable_div<R, 2>(a, U, a.m.trA[2][i] * a.m.trB[2][j], acc);
-    }
+    if (a.ign[2]) ignorable_div<R, 2>(a, U, c0, a.m.trA[2][i] * a.m.trB[2][j], acc);
 
-    finish_cell<R, GEOM>(a, U, centre_of(U), acc, GEOM == M1_CARTESIAN ? R(0) : a.m.inv_reff[i],
+    finish_cell<R, GEOM>(a, U, c0, acc, GEOM == M1_CARTESIAN ? R(0) : a.m.inv_reff[i],
                          GEOM == M1_SPHERICAL ? a.m.cot_eff[j] : R(0), id);
 }
 
@@ -314,19 +308,23 @@ __device__ __forceinline__ int task_of(int p, int tid, int nx, int ny, int &dir)
 
 // FP32 instantiations ask for at least four (default) and three (general)
 // waves per SIMD (the second argument of the bound), i.e. at most 128 and
-// 168 VGPRs: the general one just exceeds its bound otherwise, the default
-// one fits exactly.
+// 168 VGPRs; the FP64 ones for two (at most 256).
 // LIMO3 (general kernel only): each donor cell keeps two slopes per
 // direction, one for its lower and one for its upper face, and takes the
 // 32 x 8 tile in FP64 (the 512-thread block spilled).  FP32 fits three
-// waves per SIMD.  FP64 asks for two waves per SIMD: the compiler then
-// keeps the kernel within 256 registers by spilling 14-22 of them to
-// scratch, and it runs 31 % faster than unbounded at 256 VGPRs plus
-// accumulation registers, one wave per SIMD (0.276 against 0.398 ms per
-// launch on the 192x96x192 grid).
+// waves per SIMD.  FP64 keeps within 256 registers by spilling 2-10 of them
+// to scratch: one wave per SIMD with accumulation registers instead ran 31 %
+// slower.
+//
+// What bounds it: vector issue in FP32, and latency at two waves per SIMD in
+// FP64.  The closure without 1 / |F|^2, the face fix on f^2 and the regrouped
+// Riemann flux of m1_device.h took a sixth of the vector work out of each
+// face; with them a step of the 128^3 box went from 98.5 to 92.9 us (FP32) and
+// 174.6 to 153.8 us (FP64), of the 192x96x192 grid with the table in FP64
+// from 330 to 290 us, of eight groups on the 128^3 box from 535 to 495 us.
 template <typename R, int GEOM, bool GENERAL, int TYB, bool LIMO3 = false>
 __global__ void __launch_bounds__((Tile<TYB>::NT),
-                                  (sizeof(R) == 4 ? (GENERAL ? 3 : 4) : (LIMO3 ? 2 : 1)))
+                                  (sizeof(R) == 4 ? (GENERAL ? 3 : 4) : 2))
     k_transport3d(TArgs<R> a, int nz_chunk, int tiles_x, int tiles_y, int nblocks, int cus)
 {
     using T = Tile<TYB>;
@@ -391,6 +389,11 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
         ghost_fix(a, 1, y0 - 2 + hy, n1, q);
     };
 
+    // Passes 0 and 1 take the tasks numbered like the threads, so their flux
+    // and slope slots are the thread's index and the y tasks' cells lie at a
+    // fixed offset from the thread's own: those words are immediate offsets
+    // of one address and are not kept (6 registers fewer).
+    const int own = ly * HX + lx;
     // slope tasks: centre cell in sq (flat), neighbour stride, inverse spacings.
     // Cells past the last ghost (m > n) feed no face and are skipped.
     int s_ctr[NSP], s_str[NSP], s_slot[NSP];
@@ -479,14 +482,12 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
 
     // register window of the thread's column: planes k-1 .. k+2, z slope of
     // plane k.  Plane k+2 is loaded at the top of iteration k and first used
-    // after the x/y slopes (LATE): the neighbouring tiles read a plane's
+    // after the x/y slopes: the neighbouring tiles read a plane's
     // edge lines as their halo two planes after it was loaded, and those
     // lines are still in L2.  Loaded a plane earlier (k+3 in iteration k),
     // the halo read came three planes later and often missed: on the
     // 192x96x192 grid the kernel fetched 136 MB per launch instead of
-    // 99 MB, and ran 1-2 % slower.  The general FP64 kernels, at the edge
-    // of the register file, keep the earlier load (the late one spills).
-    constexpr bool LATE = !(GENERAL && sizeof(R) == 8);
+    // 99 MB, and ran 1-2 % slower.
     R W[4][4], T1, T2, Fzlo[4], Fzhi[4], Sz0[4];
     Centre<R> C1;                       // f-fix quantities of plane k (W[1])
     {
@@ -495,15 +496,12 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
         load4(a, zlin(z0 - 1, col), W[0]);
         load4(a, zlin(z0, col), W[1]);
         load4(a, zlin(z0 + 1, col), W[2]);
-        if constexpr (!LATE) load4(a, zlin(z0 + 2, col), W[3]);
         fix_col(z0 - 2, Q0);
         fix_col(z0 - 1, W[0]);
         fix_col(z0, W[1]);
         fix_col(z0 + 1, W[2]);
-        if constexpr (!LATE) fix_col(z0 + 2, W[3]);
         const R Tm = a.tau[zlin(z0 - 1, col)];
         T1 = a.tau[zlin(z0, col)];
-        if constexpr (!LATE) T2 = a.tau[zlin(z0 + 1, col)];
         C1 = centre_of(W[1]);
         if constexpr (LIMO3) {
             // the face below plane z0 takes the upper-face slope of plane
@@ -512,12 +510,12 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             R lo_m[4], lo_0[4];
             limo3_slopes4(Q0, W[0], W[1], wz[z0 + 1], wz[z0 + 2], lo_m, Szm);
             limo3_slopes4(W[0], W[1], W[2], wz[z0 + 2], wz[z0 + 3], lo_0, Sz0);
-            face_flux_s<R>(2, W[0], W[1], Szm, lo_0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm, T1,
+            face_flux_s<R>(2, W[0], W[1], Szm, lo_0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm + T1,
                            a.c_hat, Fzlo, recon, riemann);
         } else {
             slopes4(Q0, W[0], W[1], wz[z0 + 1], wz[z0 + 2], Szm);
             slopes4(W[0], W[1], W[2], wz[z0 + 2], wz[z0 + 3], Sz0);
-            face_flux_s<R>(2, W[0], W[1], Szm, Sz0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm, T1,
+            face_flux_s<R>(2, W[0], W[1], Szm, Sz0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm + T1,
                            a.c_hat, Fzlo, recon, riemann);
         }
     }
@@ -541,18 +539,10 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             else
                 __builtin_amdgcn_s_setprio(0);
         }
-        // the plane entering the window (LATE: k+2 now, else k+3 for the
-        // next iteration) and this plane's halo
-        R Qn[4], Tn = R(0);
-        if constexpr (LATE) {
-            load4(a, zlin(k + 2, col), W[3]);
-            fix_col(k + 2, W[3]);
-            T2 = a.tau[zlin(k + 1, col)];
-        } else {
-            load4(a, zlin(k + 3, col), Qn);
-            fix_col(k + 3, Qn);
-            Tn = a.tau[zlin(k + 2, col)];
-        }
+        // the plane entering the window and this plane's halo
+        load4(a, zlin(k + 2, col), W[3]);
+        fix_col(k + 2, W[3]);
+        T2 = a.tau[zlin(k + 1, col)];
         R Hq[4], Ht = R(0);
         if (tid < NHALO) {
             load4(a, k * plane + hcol, Hq);
@@ -580,22 +570,24 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             if (!s_on[p]) continue;
             R qm[4], q0[4], qp[4], sl[4];
             const int str = p == 0 ? 1 : (p == 1 ? HX : s_str[p]);
+            const int ctr = p == 1 ? own + HX + 2 : s_ctr[p];
+            const int slot = p == 0 ? tid : (p == 1 ? NXS + tid : s_slot[p]);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                qm[v] = sqf[v * QS + s_ctr[p] - str];
-                q0[v] = sqf[v * QS + s_ctr[p]];
-                qp[v] = sqf[v * QS + s_ctr[p] + str];
+                qm[v] = sqf[v * QS + ctr - str];
+                q0[v] = sqf[v * QS + ctr];
+                qp[v] = sqf[v * QS + ctr + str];
             }
             if constexpr (LIMO3) {
                 R lo[4];
                 limo3_slopes4(qm, q0, qp, s_wl[p], s_wr[p], lo, sl);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) ssl[v][s_slot[p]] = lo[v];
+                for (int v = 0; v < 4; ++v) ssl[v][slot] = lo[v];
             } else {
                 slopes4(qm, q0, qp, s_wl[p], s_wr[p], sl);
             }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) ss[v][s_slot[p]] = sl[v];
+            for (int v = 0; v < 4; ++v) ss[v][slot] = sl[v];
         }
         // z slope(s) of plane k+1 (LimO3: Sz1 its upper-face slope, Sz1l
         // its lower-face one)
@@ -610,7 +602,9 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
 #pragma unroll
         for (int p = 0; p < NFP; ++p) {
             if (!f_on[p]) continue;
-            const int d = p < 2 ? p : f_d[p], b = f_b[p], sb = f_sb[p];
+            const int d = p < 2 ? p : f_d[p];
+            const int b = p == 1 ? own + HX + 2 : f_b[p], sb = p == 1 ? NXS + tid : f_sb[p];
+            const int fo = p < 2 ? tid : f_o[p];
             const int qst = d ? HX : 1, sst = d ? TX : 1;
             R qb[4], qc[4], slb[4], slc[4], fl[4];
 #pragma unroll
@@ -621,15 +615,15 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
                 slc[v] = LIMO3 ? ssl[v][sb + sst] : ss[v][sb + sst];
             }
             face_flux_s<R>(d, qb, qc, slb, slc, Centre<R>{scf2[b], scie[b]}, Centre<R>{scf2[b + qst], scie[b + qst]},
-                           f_hp[p], f_hm[p], stf[b], stf[b + qst], a.c_hat, fl, recon, riemann);
+                           f_hp[p], f_hm[p], stf[b] + stf[b + qst], a.c_hat, fl, recon, riemann);
             R *dst = d ? &sfy[0][0][0] : &sfx[0][0][0];
             const int fs = d ? (TY + 1) * TX : TY * (TX + 1);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) dst[v * fs + f_o[p]] = fl[v];
+            for (int v = 0; v < 4; ++v) dst[v * fs + fo] = fl[v];
         }
         // z face above the plane from the register window
         const Centre<R> C2 = centre_of(W[2]);
-        face_flux_s<R>(2, W[1], W[2], Sz0, LIMO3 ? Sz1l : Sz1, C1, C2, hpz[k + 2], hmz[k + 3], T1, T2, a.c_hat,
+        face_flux_s<R>(2, W[1], W[2], Sz0, LIMO3 ? Sz1l : Sz1, C1, C2, hpz[k + 2], hmz[k + 3], T1 + T2, a.c_hat,
                        Fzhi, recon, riemann);
         __syncthreads();
 
@@ -650,10 +644,8 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             W[0][v] = W[1][v];
             W[1][v] = W[2][v];
             W[2][v] = W[3][v];
-            if constexpr (!LATE) W[3][v] = Qn[v];
         }
         T1 = T2;
-        if constexpr (!LATE) T2 = Tn;
         C1 = C2;
     }
 }
