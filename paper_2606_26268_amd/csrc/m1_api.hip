@@ -51,7 +51,7 @@ static m1_status hip_fail(hipError_t e, const char *what)
 // --------------------------------------------------------------------------
 
 struct HostMetric {
-    std::vector<double> winv[3], hp[3], hm[3], alo[3], ahi[3], trA[3], trB[3], hd[3], hI[3], hJ[3];
+    std::vector<double> rat[3], hp[3], hm[3], alo[3], ahi[3], trA[3], trB[3], hd[3], hI[3], hJ[3];
     std::vector<double> inv_reff, cot_eff, vol[3];
 };
 
@@ -94,17 +94,19 @@ static void build_metric(const m1_ctx *c, HostMetric &M)
     const int n0 = c->n[0], n1 = c->n[1];
     for (int d = 0; d < 3; ++d) {
         const int n = c->n[d];
-        M.winv[d].assign(n + 4, 0.0);
+        M.rat[d].assign(n + 4, 0.0);
         M.hp[d].assign(n + 4, 0.0);
         M.hm[d].assign(n + 4, 0.0);
         double plo, pce, phi;
         ghost_coords(c, d, -2, plo, pce, phi);
-        for (int t = -1; t <= n + 1; ++t) {
-            double lo, ce, hi;
+        for (int t = -1; t <= n; ++t) {
+            double lo, ce, hi, nlo, nce, nhi;
             ghost_coords(c, d, t, lo, ce, hi);
-            M.winv[d][t + 2] = 1.0 / (ce - pce);
-            M.hp[d][t + 2] = hi - ce;
-            M.hm[d][t + 2] = ce - lo;
+            ghost_coords(c, d, t + 1, nlo, nce, nhi);
+            const double D = ce - pce;
+            M.rat[d][t + 2] = D / (nce - ce);
+            M.hp[d][t + 2] = (hi - ce) / D;
+            M.hm[d][t + 2] = (ce - lo) / D;
             pce = ce;
         }
         M.alo[d].assign(n, 0.0);
@@ -183,7 +185,7 @@ static m1_status upload_metric(m1_ctx *c, const HostMetric &M)
 {
     std::vector<const std::vector<double> *> arrs;
     for (int d = 0; d < 3; ++d) {
-        arrs.push_back(&M.winv[d]);
+        arrs.push_back(&M.rat[d]);
         arrs.push_back(&M.hp[d]);
         arrs.push_back(&M.hm[d]);
         arrs.push_back(&M.alo[d]);
@@ -219,7 +221,7 @@ static m1_status upload_metric(m1_ctx *c, const HostMetric &M)
     auto p32 = [&](size_t a) { return reinterpret_cast<const float *>(base + off32[a]); };
     for (int d = 0; d < 3; ++d) {
         const size_t b = 10 * d;
-        c->met64.winv[d] = p64(b + 0); c->met32.winv[d] = p32(b + 0);
+        c->met64.rat[d] = p64(b + 0);  c->met32.rat[d] = p32(b + 0);
         c->met64.hp[d] = p64(b + 1);   c->met32.hp[d] = p32(b + 1);
         c->met64.hm[d] = p64(b + 2);   c->met32.hm[d] = p32(b + 2);
         c->met64.alo[d] = p64(b + 3);  c->met32.alo[d] = p32(b + 3);

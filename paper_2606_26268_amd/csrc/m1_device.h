@@ -108,21 +108,14 @@ struct Face {
 
 // f-preserving fix of a reconstructed face state U against its donor cell C
 // (Eq. f_reconstruct): keep F_face iff f_face <= 1 and f_face > f_centre,
-// else F_face = F_c E_f / E_c; E_face <= 0 falls back to the centre state.
-// The comparison is made on f^2, which the closure needs in either case (the
+// else F_face = F_c E_f / E_c (E_face > 0).  The comparison is made on f^2, which the closure needs in either case (the
 // rescaled state has the centre's), so it costs no operation of its own.
 template <typename R>
 __device__ __forceinline__ Face<R> ffix(const R U[4], const R C[4], Centre<R> cc)
 {
-    Face<R> s;
-    const bool pos = U[0] > R(0);
-    s.E = pos ? U[0] : C[0];
-    s.ie = Num<R>::rcp(s.E);
+    Face<R> s{U[0], {U[1], U[2], U[3]}, R(0), Num<R>::rcp(U[0])};
     s.f2 = (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]) * s.ie * s.ie;
-    s.F[0] = U[1];
-    s.F[1] = U[2];
-    s.F[2] = U[3];
-    if (!(pos && s.f2 <= R(1) && s.f2 > cc.f2)) {
+    if (!(s.f2 <= R(1) && s.f2 > cc.f2)) {
         const R r = s.E * cc.ie;
         s.F[0] = C[1] * r;
         s.F[1] = C[2] * r;
@@ -166,13 +159,13 @@ __device__ __forceinline__ R along(int d, R x, R y, R z)
 
 // Closure of a face state seen from direction d (Sect. 2.1, 2.6), all in units
 // of c_hat: signal speeds lm <= lp and the flux as
-//   Phi_0 = F_d,  Phi_q = c F_q + (q = d) iso.
+//   Phi_0 = F_d,  Phi_q = c F_q + (q = d) iso / 3.
 // With s = sqrt(4 - 3 f^2) Levermore's xi is (5 - 2 s) / 3, so that
 // (1 - xi) / 2 = (s - 1) / 3 and (3 xi - 1) / 2 = 2 - s.  2 - s vanishes with
 // f^2, as 3 f^2 / (2 + s), which takes 1 / |F|^2 out of every expression: with
-// phi = F_d / E and m = phi / (2 + s),
-//   c      = (2 - s) E F_d / |F|^2        = 3 m,
-//   zeta^2 = 2 (s - 1) (s / 3 - phi m)     (lambda_-+ = (phi -+ zeta) / s).
+// phi = F_d / E and m = 2 phi / (2 + s),
+//   c      = (2 - s) E F_d / |F|^2      = 3 m / 2,
+//   zeta^2 = (s - 1) (2 s / 3 - phi m)   (lambda_-+ = (phi -+ zeta) / s).
 // No direction n = F / |F| is formed, so F = 0 and fluxes whose square is
 // below the normal range need no case of their own, and the difference 2 - s
 // of nearly equal numbers at small f is gone.  f > 1 (a centre state past the
@@ -209,22 +202,23 @@ __device__ __forceinline__ Wave<R> closure_of(const Face<R> &u, int d, R k)
         s = Num<R>::sqrt_(s2);
         is = Num<R>::rcp(s);
     }
-    const R m = phi * Num<R>::rcp(R(2) + s);
+    const R m = phi * Num<R>::rcp(R(1) + R(0.5) * s);
     const R g = s - R(1);
     // the lower bound keeps the FP64 square root's argument normal
-    const R zeta = Num<R>::sqrt_pos(vmax((g + g) * (R(1.0 / 3.0) * s - phi * m), Num<R>::tiny));
+    const R zeta = Num<R>::sqrt_pos(vmax(g * (R(2.0 / 3.0) * s - phi * m), Num<R>::tiny));
     w.lm = (phi - zeta) * is;
     w.lp = (phi + zeta) * is;
     w.c = k * m;
-    w.iso = g * (R(1.0 / 3.0) * u.E);
+    w.iso = g * u.E;
     return w;
 }
 
-// Interface flux c_hat Phi* between two face states L | R (Sect. 2.5): HLL
+// Interface flux Phi* between two face states L | R (Sect. 2.5) in units of
+// c_hat: HLL
 // with lambda_L = min lambda_-, lambda_R = max lambda_+ clamped to -+4/(3 tau)
 // (Sect. 2.6), S_L = min(lambda_L, 0), S_R = max(lambda_R, 0), the average flux
 // for S_L = S_R = 0; or Lax-Friedrichs-Rusanov, which is HLL with S_R = -S_L
-// the largest limited speed magnitude.  With k = c_hat / (S_R - S_L),
+// the largest limited speed magnitude.  With k = 1 / (S_R - S_L),
 // a = k S_R and b = -k S_L,
 //   k (S_R Phi_L - S_L Phi_R + S_L S_R (U_R - U_L))
 //     = a (c_L - S_L) F_L + b (c_R - S_R) F_R + (q = d) (a iso_L + b iso_R)
@@ -235,10 +229,10 @@ __device__ __forceinline__ Wave<R> closure_of(const Face<R> &u, int d, R k)
 // 8 / (3 tau_sum), and as |lambda| <= 1 the limit is without effect for
 // tau_sum below 1, which keeps the reciprocal finite at tau = 0.
 template <typename R>
-__device__ __forceinline__ void interface_flux(int d, Face<R> l, Face<R> r, R tau_sum, R c_hat,
-                                               R out[4], int riemann)
+__device__ __forceinline__ void interface_flux(int d, Face<R> l, Face<R> r, R tau_sum, R out[4],
+                                               int riemann)
 {
-    R kl = R(3), kr = R(3);
+    R kl = R(1.5), kr = R(1.5);
     if (vmax(l.f2, r.f2) > R(1)) {
         limit_f(l, kl);
         limit_f(r, kr);
@@ -247,18 +241,18 @@ __device__ __forceinline__ void interface_flux(int d, Face<R> l, Face<R> r, R ta
     const R lim = R(8.0 / 3.0) * Num<R>::rcp(vmax(tau_sum, R(1)));
     R SL = vmax(vmin(vmin(wl.lm, wr.lm), R(0)), -lim);
     R SR = vmin(vmax(vmax(wl.lp, wr.lp), R(0)), lim);
-    R a = R(0.5) * c_hat, b = a;
+    R a = R(0.5), b = a;
     if (riemann == M1_RIEMANN_LF) {
         const R lamL = vmax(vmin(wl.lm, wr.lm), -lim), lamR = vmin(vmax(wl.lp, wr.lp), lim);
         SR = vmax(__builtin_fabs(lamL), __builtin_fabs(lamR));
         SL = -SR;
     } else if (SR > SL) {
-        const R k = c_hat * Num<R>::rcp(SR - SL);
+        const R k = Num<R>::rcp(SR - SL);
         a = k * SR;
         b = -(k * SL);
     }
     const R el = a * (wl.c - SL), er = b * (wr.c - SR);
-    const R iso = a * wl.iso + b * wr.iso;
+    const R iso = R(1.0 / 3.0) * (a * wl.iso + b * wr.iso);
     const R Fl = along(d, l.F[0], l.F[1], l.F[2]), Fr = along(d, r.F[0], r.F[1], r.F[2]);
     out[0] = (a * SL) * (r.E - l.E) + (a * Fl + b * Fr);
 #pragma unroll
@@ -269,11 +263,16 @@ __device__ __forceinline__ void interface_flux(int d, Face<R> l, Face<R> r, R ta
 // intrinsic, so its scheduling and hazard rules apply)
 extern "C" __device__ float amdgcn_fmul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
 
-// van Leer limited slope without a branch, as
-// (dl |dr| + |dl| dr) / (|dl| + |dr|): the harmonic mean 2 dl dr / (dl + dr)
-// when the signs agree, zero when they differ or either is zero.  FP32 uses
-// the legacy multiply (0 x inf = 0), so dl = dr = 0 gives 0 without a select
-// (and a subnormal |dl| + |dr|, whose reciprocal overflows, has num = 0).
+// van Leer limited slope without a branch: the harmonic mean
+// 2 dl dr / (dl + dr) when the signs agree, zero when they differ or either
+// is zero.  FP32: (dl |dr| + |dl| dr) / (|dl| + |dr|) with the legacy multiply
+// (0 x inf = 0), so dl = dr = 0 gives 0 without a select (and a subnormal
+// |dl| + |dr|, whose reciprocal overflows, has num = 0).  FP64: 2 u w (dl + dr)
+// with the shares u = dl / (dl + dr) and w = dr / (dl + dr) clamped to
+// [0, 1], which costs nothing (an output modifier): of opposite signs one
+// share is negative, and of dl + dr = 0 both are NaN, which the clamp takes
+// to 0; no compare and select, and no product of two small differences that
+// could underflow.
 template <typename R>
 __device__ __forceinline__ R vanleer_fast(R dl, R dr);
 template <>
@@ -285,20 +284,19 @@ __device__ __forceinline__ float vanleer_fast<float>(float dl, float dr)
 template <>
 __device__ __forceinline__ double vanleer_fast<double>(double dl, double dr)
 {
-    const double den = __builtin_fabs(dl) + __builtin_fabs(dr);
-    const double num = __builtin_fma(__builtin_fabs(dl), dr, dl * __builtin_fabs(dr));
-    // |dl| + |dr| under the smallest normal number gives 0 (the limited
-    // slope is below half of it), keeping the reciprocal finite
-    return den >= Num<double>::tiny ? num * Num<double>::rcp(den) : 0.0;
+    const double den = dl + dr, t = Num<double>::rcp(den);
+    const double u = __builtin_fmin(__builtin_fmax(dl * t, 0.0), 1.0);
+    const double w = __builtin_fmin(__builtin_fmax(dr * t, 0.0), 1.0);
+    return (u * w) * (den + den);
 }
 
 // Flux at the face between donor cells b (left) and c (right) along d from
-// their states, slopes (sb, sc; per unit length) and f-fix quantities (cb,
+// their states, slopes (sb, sc; per lower spacing) and f-fix quantities (cb,
 // cc): face states q_b + s_b hp_b and q_c - s_c hm_c, the face treatment, both
 // closures and the optical-depth-limited flux.
 template <typename R>
 __device__ __forceinline__ void face_flux_s(int d, const R qb[4], const R qc[4], const R sb[4], const R sc[4],
-                                            Centre<R> cb, Centre<R> cc, R hpL, R hmR, R tau_sum, R c_hat,
+                                            Centre<R> cb, Centre<R> cc, R hpL, R hmR, R tau_sum,
                                             R out[4], int recon = M1_RECON_FPRESERVE,
                                             int riemann = M1_RIEMANN_HLL)
 {
@@ -310,22 +308,33 @@ __device__ __forceinline__ void face_flux_s(int d, const R qb[4], const R qc[4],
     }
     Face<R> l, r;
     if (recon == M1_RECON_FPRESERVE) {
+        // E_face <= 0 (no limited slope gives it on a positive field) falls
+        // back to the centre state, which the fix then leaves as it is
+        const bool pl = UL[0] > R(0), pr = UR[0] > R(0);
+        if (!(vmin(UL[0], UR[0]) > R(0))) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                UL[v] = pl ? UL[v] : qb[v];
+                UR[v] = pr ? UR[v] : qc[v];
+            }
+        }
         l = ffix(UL, qb, cb);
         r = ffix(UR, qc, cc);
     } else {
         l = face_fix(recon, UL, qb);
         r = face_fix(recon, UR, qc);
     }
-    interface_flux(d, l, r, tau_sum, c_hat, out, riemann);
+    interface_flux(d, l, r, tau_sum, out, riemann);
 }
 
 // van Leer slopes of the four fields of cell m from cells m-1, m, m+1 and the
-// inverse centre spacings wl = 1/(x_m - x_{m-1}), wr = 1/(x_{m+1} - x_m).
+// ratio of its centre spacings (x_m - x_{m-1}) / (x_{m+1} - x_m); per lower
+// spacing, as are the limiter's arguments (it is homogeneous of degree one).
 template <typename R>
-__device__ __forceinline__ void slopes4(const R qm[4], const R q0[4], const R qp[4], R wl, R wr, R s[4])
+__device__ __forceinline__ void slopes4(const R qm[4], const R q0[4], const R qp[4], R rat, R s[4])
 {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) s[v] = vanleer_fast((q0[v] - qm[v]) * wl, (qp[v] - q0[v]) * wr);
+    for (int v = 0; v < 4; ++v) s[v] = vanleer_fast(q0[v] - qm[v], (qp[v] - q0[v]) * rat);
 }
 
 // LimO3 limited slope (Cada and Torrilhon 2009, the compact third-order
@@ -351,12 +360,12 @@ __device__ __forceinline__ R limo3(R dfar, R dnear)
 // LimO3 slopes of the four fields of cell m from cells m-1, m, m+1: lo for
 // the lower face (near side m-1), hi for the upper face (near side m+1).
 template <typename R>
-__device__ __forceinline__ void limo3_slopes4(const R qm[4], const R q0[4], const R qp[4], R wl, R wr, R lo[4],
+__device__ __forceinline__ void limo3_slopes4(const R qm[4], const R q0[4], const R qp[4], R rat, R lo[4],
                                               R hi[4])
 {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const R dl = (q0[v] - qm[v]) * wl, dr = (qp[v] - q0[v]) * wr;
+        const R dl = q0[v] - qm[v], dr = (qp[v] - q0[v]) * rat;
         hi[v] = limo3(dl, dr);
         lo[v] = limo3(dr, dl);
     }

@@ -15,9 +15,12 @@ namespace m1 {
 // entries on each side (index t + 2 for t in [-2, n+1]).
 template <typename R>
 struct Metric {
-    const R *winv[3];  // 1 / (x_t - x_{t-1}) between centres, t in [-1, n+1]
-    const R *hp[3];    // x_{t+1/2} - x_t
-    const R *hm[3];    // x_t - x_{t-1/2}
+    // with the centre spacing D_t = x_t - x_{t-1}, t in [-1, n]: slopes are
+    // limited in units of the cell's lower spacing, so that one difference of
+    // the two needs a factor instead of both
+    const R *rat[3];   // D_t / D_{t+1}
+    const R *hp[3];    // (x_{t+1/2} - x_t) / D_t
+    const R *hm[3];    // (x_t - x_{t-1/2}) / D_t
     // face area over cell volume for direction d:
     //   A_lo/V = alo[d][t] * trA[d][i] * trB[d][j], A_hi/V likewise with ahi
     const R *alo[3], *ahi[3], *trA[3], *trB[3];

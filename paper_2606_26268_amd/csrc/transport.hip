@@ -129,35 +129,28 @@ __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int s
         load4(a, li[s], q[s]);
         if (a.special) ghost_fix(a, D, t - 2 + s, n, q[s]);
     }
-    const R *winv = a.m.winv[D], *hp = a.m.hp[D], *hm = a.m.hm[D];
+    const R *rat = a.m.rat[D], *hp = a.m.hp[D], *hm = a.m.hm[D];
     // slopes: cell t-1 for its upper face, cell t for its lower and upper
     // faces, cell t+1 for its lower face
     R sm[4], slo[4], shi[4], sp[4];
+    if (a.limo3) {
+        R other[4];
+        limo3_slopes4(q[0], q[1], q[2], rat[t + 1], other, sm);
+        limo3_slopes4(q[1], q[2], q[3], rat[t + 2], slo, shi);
+        limo3_slopes4(q[2], q[3], q[4], rat[t + 3], sp, other);
+    } else {
+        slopes4(q[0], q[1], q[2], rat[t + 1], sm);
+        slopes4(q[1], q[2], q[3], rat[t + 2], slo);
+        slopes4(q[2], q[3], q[4], rat[t + 3], sp);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const R dA = (q[1][v] - q[0][v]) * winv[t + 1];
-        const R dB = (q[2][v] - q[1][v]) * winv[t + 2];
-        const R dC = (q[3][v] - q[2][v]) * winv[t + 3];
-        const R dD = (q[4][v] - q[3][v]) * winv[t + 4];
-        if (a.limo3) {
-            // each face takes its own slope: the difference on the face side
-            // is the near one
-            sm[v] = limo3(dA, dB);
-            slo[v] = limo3(dC, dB);
-            shi[v] = limo3(dB, dC);
-            sp[v] = limo3(dD, dC);
-        } else {
-            sm[v] = vanleer_fast(dA, dB);
-            slo[v] = shi[v] = vanleer_fast(dB, dC);
-            sp[v] = vanleer_fast(dC, dD);
-        }
+        for (int v = 0; v < 4; ++v) shi[v] = slo[v];
     }
     const R tm = a.tau[li[1]], t0 = a.tau[li[2]], tp = a.tau[li[3]];
     const Centre<R> cm = centre_of(q[1]), cp = centre_of(q[3]);
     R flo[4], fhi[4];
-    face_flux_s<R>(D, q[1], q[2], sm, slo, cm, c0, hp[t + 1], hm[t + 2], tm + t0, a.c_hat, flo, a.recon, a.riemann);
-    face_flux_s<R>(D, q[2], q[3], shi, sp, c0, cp, hp[t + 2], hm[t + 3], t0 + tp, a.c_hat, fhi, a.recon, a.riemann);
-    const R al = a.m.alo[D][t] * tr, ah = a.m.ahi[D][t] * tr;
+    face_flux_s<R>(D, q[1], q[2], sm, slo, cm, c0, hp[t + 1], hm[t + 2], tm + t0, flo, a.recon, a.riemann);
+    face_flux_s<R>(D, q[2], q[3], shi, sp, c0, cp, hp[t + 2], hm[t + 3], t0 + tp, fhi, a.recon, a.riemann);
+    const R al = a.m.alo[D][t] * tr, ah = a.m.ahi[D][t] * tr;   // tr carries dt c_hat
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] += face_diff<same_area<GEOM, D>>(al, ah, flo[v], fhi[v]);
 }
@@ -166,24 +159,25 @@ template <typename R, int D>
 __device__ __forceinline__ void ignorable_div(const TArgs<R> &a, const R U[4], Centre<R> c0, R tr, R acc[4])
 {
     Face<R> u{U[0], {U[1], U[2], U[3]}, c0.f2, c0.ie};
-    R k = R(3);
+    R k = R(1.5);
     limit_f(u, k);
     const Wave<R> w = closure_of(u, D, k);
-    const R dA = (a.m.ahi[D][0] - a.m.alo[D][0]) * tr * a.c_hat;
+    const R dA = (a.m.ahi[D][0] - a.m.alo[D][0]) * tr;
     acc[0] += dA * U[1 + D];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[1 + q] += dA * (w.c * U[1 + q] + (q == D ? w.iso : R(0)));
+    for (int q = 0; q < 3; ++q) acc[1 + q] += dA * (w.c * U[1 + q] + (q == D ? R(1.0 / 3.0) * w.iso : R(0)));
 }
 
-// U* = U - dt div(Phi) + dt c_hat S_geo(U), then E >= floor and f <= 1
-// (counted), stored to the transported state.
+// U* = U - acc + dt c_hat S_geo(U), acc = dt div(Phi) (the fluxes come in units
+// of c_hat and the area factors carry dt c_hat), then E >= floor and f <= 1
+// (counted), stored to the transported state of cell id.
 template <typename R, int GEOM>
 __device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Centre<R> cu, const R acc[4], R ir, R ct,
                                             int id)
 {
     R Us[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Us[v] = U[v] - a.dt * acc[v];
+    for (int v = 0; v < 4; ++v) Us[v] = U[v] - acc[v];
 
     if (GEOM != M1_CARTESIAN) {
         // geometric sources from the cell-centre pressure tensor
@@ -245,14 +239,15 @@ __global__ void __launch_bounds__(256) k_transport(TArgs<R> a)
     R acc[4] = {R(0), R(0), R(0), R(0)};
     const Centre<R> c0 = centre_of(U);
 
-    direction_div<R, 0, GEOM>(a, id - i, 1, i, R(1), c0, acc);
+    const R dtc = a.dt * a.c_hat;
+    direction_div<R, 0, GEOM>(a, id - i, 1, i, dtc, c0, acc);
     if (NDIM >= 2) {
-        const R tr = a.m.trA[1][i];
+        const R tr = a.m.trA[1][i] * dtc;
         direction_div<R, 1, GEOM>(a, id - j * n0, n0, j, tr, c0, acc);
     } else if (a.ign[1]) {
-        ignorable_div<R, 1>(a, U, c0, a.m.trA[1][i], acc);
+        ignorable_div<R, 1>(a, U, c0, a.m.trA[1][i] * dtc, acc);
     }
-    if (a.ign[2]) ignorable_div<R, 2>(a, U, c0, a.m.trA[2][i] * a.m.trB[2][j], acc);
+    if (a.ign[2]) ignorable_div<R, 2>(a, U, c0, a.m.trA[2][i] * a.m.trB[2][j] * dtc, acc);
 
     finish_cell<R, GEOM>(a, U, c0, acc, GEOM == M1_CARTESIAN ? R(0) : a.m.inv_reff[i],
                          GEOM == M1_SPHERICAL ? a.m.cot_eff[j] : R(0), id);
@@ -312,16 +307,24 @@ __device__ __forceinline__ int task_of(int p, int tid, int nx, int ny, int &dir)
 // LIMO3 (general kernel only): each donor cell keeps two slopes per
 // direction, one for its lower and one for its upper face, and takes the
 // 32 x 8 tile in FP64 (the 512-thread block spilled).  FP32 fits three
-// waves per SIMD.  FP64 keeps within 256 registers by spilling 2-10 of them
-// to scratch: one wave per SIMD with accumulation registers instead ran 31 %
-// slower.
+// waves per SIMD.  FP64 keeps within 256 registers (the spherical kernel by
+// spilling a few to scratch): one wave per SIMD with accumulation registers
+// instead ran 31 % slower.
 //
-// What bounds it: vector issue in FP32, and latency at two waves per SIMD in
-// FP64.  The closure without 1 / |F|^2, the face fix on f^2 and the regrouped
-// Riemann flux of m1_device.h took a sixth of the vector work out of each
-// face; with them a step of the 128^3 box went from 98.5 to 92.9 us (FP32) and
-// 174.6 to 153.8 us (FP64), of the 192x96x192 grid with the table in FP64
-// from 330 to 290 us, of eight groups on the 128^3 box from 535 to 495 us.
+// What bounds it: vector issue, in FP32 (about 600 operations a cell and
+// plane, 50 of them transcendental at two slots and a third) and in FP64
+// (about 1000, at the 1.85 GHz or so that FP64 work leaves the clock at).  A
+// step of the 128^3 box went from 99 to 92.9 us (FP32) and 176 to 153.8 us
+// (FP64) with the closure without 1 / |F|^2, the face fix on f^2 and the
+// regrouped Riemann flux of m1_device.h, and on to 88.5 and 143.5 us with one
+// spacing factor per slope, dt c_hat in the area factors, one code block for
+// the first two task passes and the halo loaded a plane ahead; 192x96x192
+// with the table in FP64 330 -> 290 -> 270 us, eight groups on the 128^3 box
+// 536 -> 495 -> 460 us.  Tried and not kept: two or three planes per turn of the
+// loop (no register moves; the FP32 kernels spilled and ran 15 % slower, FP64
+// was equal); scalar bases with a 32-bit lane offset for the plane loads and
+// stores (4 % slower); selects in place of the branches of the face fix and
+// the Riemann flux (equal).
 template <typename R, int GEOM, bool GENERAL, int TYB, bool LIMO3 = false>
 __global__ void __launch_bounds__((Tile<TYB>::NT),
                                   (sizeof(R) == 4 ? (GENERAL ? 3 : 4) : 2))
@@ -394,35 +397,36 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     // fixed offset from the thread's own: those words are immediate offsets
     // of one address and are not kept (6 registers fewer).
     const int own = ly * HX + lx;
-    // slope tasks: centre cell in sq (flat), neighbour stride, inverse spacings.
-    // Cells past the last ghost (m > n) feed no face and are skipped.
+    // slope tasks: centre cell in sq (flat), neighbour stride, spacing ratio.
+    // Cells past the last ghost (m > n) feed no face that is used: passes 0
+    // and 1 run them along (on staged cells and a zero ratio) rather than
+    // split the code into one block per pass, pass 2 is left to the
+    // wavefronts that have tasks in it.
     int s_ctr[NSP], s_str[NSP], s_slot[NSP];
-    R s_wl[NSP], s_wr[NSP];
-    bool s_on[NSP];
+    R s_rat[NSP];
+    bool s_on = false;
 #pragma unroll
     for (int p = 0; p < NSP; ++p) {
         int dir;
+        s_on = false;                   // the last pass decides
         const int q = task_of<NT>(p, tid, NXS, NYS, dir);
-        s_on[p] = false;
         s_ctr[p] = 2 * HX + 2;
         s_str[p] = 1;
-        s_wl[p] = s_wr[p] = R(0);
+        s_rat[p] = R(0);
         if (q >= 0 && dir == 0) {
             const int r = q / (TX + 2), c = q % (TX + 2), m = x0 + c - 1;
             if (m <= n0) {
-                s_on[p] = true;
+                s_on = true;
                 s_ctr[p] = (r + 2) * HX + c + 1;
-                s_wl[p] = a.m.winv[0][m + 2];
-                s_wr[p] = a.m.winv[0][m + 3];
+                s_rat[p] = a.m.rat[0][m + 2];
             }
         } else if (q >= 0) {
             const int qq = q, r = qq / TX, c = qq % TX, m = y0 + r - 1;
             if (m <= n1) {
-                s_on[p] = true;
+                s_on = true;
                 s_ctr[p] = (r + 1) * HX + c + 2;
                 s_str[p] = HX;
-                s_wl[p] = a.m.winv[1][m + 2];
-                s_wr[p] = a.m.winv[1][m + 3];
+                s_rat[p] = a.m.rat[1][m + 2];
             }
         }
         s_slot[p] = dir == 0 ? q : NXS + q;
@@ -431,19 +435,19 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     // centre-to-face offsets of the two donors
     int f_d[NFP], f_b[NFP], f_sb[NFP], f_o[NFP];
     R f_hp[NFP], f_hm[NFP];
-    bool f_on[NFP];
+    bool f_on = false;
 #pragma unroll
     for (int p = 0; p < NFP; ++p) {
         int dir;
+        f_on = false;
         const int q = task_of<NT>(p, tid, NXF, NYF, dir);
-        f_on[p] = false;
         f_d[p] = 0;
         f_b[p] = f_sb[p] = f_o[p] = 0;
         f_hp[p] = f_hm[p] = R(0);
         if (q >= 0 && dir == 0) {
             const int row = q / (TX + 1), fo = q % (TX + 1), g = x0 + fo;
             if (g <= n0 && y0 + row < n1) {
-                f_on[p] = true;
+                f_on = true;
                 f_b[p] = (row + 2) * HX + fo + 1;
                 f_sb[p] = row * (TX + 2) + fo;
                 f_o[p] = row * (TX + 1) + fo;
@@ -453,7 +457,7 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
         } else if (q >= 0) {
             const int qq = q, go = qq / TX, cl = qq % TX, g = y0 + go;
             if (g <= n1 && x0 + cl < n0) {
-                f_on[p] = true;
+                f_on = true;
                 f_d[p] = 1;
                 f_b[p] = (go + 1) * HX + cl + 2;
                 f_sb[p] = NXS + go * TX + cl;
@@ -463,22 +467,28 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             }
         }
     }
-    // update factors of the thread's column
+    // update factors of the thread's column, dt c_hat among them
     R axl = R(0), axh = R(0), ayl = R(0), ayh = R(0), tr2 = R(0), ir = R(0), ct = R(0);
     if (live) {
-        axl = a.m.alo[0][i];
-        axh = a.m.ahi[0][i];
-        const R tr1 = a.m.trA[1][i];
+        const R dtc = a.dt * a.c_hat;
+        axl = a.m.alo[0][i] * dtc;
+        axh = a.m.ahi[0][i] * dtc;
+        const R tr1 = a.m.trA[1][i] * dtc;
         ayl = a.m.alo[1][j] * tr1;
         ayh = a.m.ahi[1][j] * tr1;
-        tr2 = a.m.trA[2][i] * a.m.trB[2][j];
+        tr2 = a.m.trA[2][i] * a.m.trB[2][j] * dtc;
         if (GEOM != M1_CARTESIAN) ir = a.m.inv_reff[i];
         if (GEOM == M1_SPHERICAL) ct = a.m.cot_eff[j];
     }
 
     const int bz0 = a.bc[2][0], bz1 = a.bc[2][1];
-    auto zlin = [&](int kk, int c) { return map_index(kk, n2, bz0, bz1) * plane + c; };
-    const R *wz = a.m.winv[2], *hpz = a.m.hp[2], *hmz = a.m.hm[2];
+    // cell c of plane kk (mapped) and its optical depth
+    auto loadp = [&](int kk, int c, R q[4], R &t) {
+        const int lin = map_index(kk, n2, bz0, bz1) * plane + c;
+        load4(a, lin, q);
+        t = a.tau[lin];
+    };
+    const R *rz = a.m.rat[2], *hpz = a.m.hp[2], *hmz = a.m.hm[2];
 
     // register window of the thread's column: planes k-1 .. k+2, z slope of
     // plane k.  Plane k+2 is loaded at the top of iteration k and first used
@@ -488,35 +498,36 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     // the halo read came three planes later and often missed: on the
     // 192x96x192 grid the kernel fetched 136 MB per launch instead of
     // 99 MB, and ran 1-2 % slower.
-    R W[4][4], T1, T2, Fzlo[4], Fzhi[4], Sz0[4];
-    Centre<R> C1;                       // f-fix quantities of plane k (W[1])
+    // Halo cells are loaded one plane ahead: issued after the staging of plane
+    // k, they arrive while its faces are computed.
+    R W0[4], W1[4], T0, T1, Fz0[4], Fz1[4], Sz0[4], Sz1[4], Hq[4], Ht = R(0);
+    Centre<R> C0, C1;                   // f-fix quantities of plane k and k + 1
     {
-        R Q0[4], Szm[4];
-        load4(a, zlin(z0 - 2, col), Q0);
-        load4(a, zlin(z0 - 1, col), W[0]);
-        load4(a, zlin(z0, col), W[1]);
-        load4(a, zlin(z0 + 1, col), W[2]);
+        R Q0[4], Qm[4], Szm[4], Tm, Tx;
+        loadp(z0 - 2, col, Q0, Tx);
+        loadp(z0 - 1, col, Qm, Tm);
+        loadp(z0, col, W0, T0);
+        loadp(z0 + 1, col, W1, T1);
+        if (tid < NHALO) loadp(z0, hcol, Hq, Ht);
         fix_col(z0 - 2, Q0);
-        fix_col(z0 - 1, W[0]);
-        fix_col(z0, W[1]);
-        fix_col(z0 + 1, W[2]);
-        const R Tm = a.tau[zlin(z0 - 1, col)];
-        T1 = a.tau[zlin(z0, col)];
-        C1 = centre_of(W[1]);
+        fix_col(z0 - 1, Qm);
+        fix_col(z0, W0);
+        fix_col(z0 + 1, W1);
+        C0 = centre_of(W0);
         if constexpr (LIMO3) {
             // the face below plane z0 takes the upper-face slope of plane
             // z0 - 1 and the lower-face slope of plane z0; Sz0 carries the
             // upper-face slope of the current plane
             R lo_m[4], lo_0[4];
-            limo3_slopes4(Q0, W[0], W[1], wz[z0 + 1], wz[z0 + 2], lo_m, Szm);
-            limo3_slopes4(W[0], W[1], W[2], wz[z0 + 2], wz[z0 + 3], lo_0, Sz0);
-            face_flux_s<R>(2, W[0], W[1], Szm, lo_0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm + T1,
-                           a.c_hat, Fzlo, recon, riemann);
+            limo3_slopes4(Q0, Qm, W0, rz[z0 + 1], lo_m, Szm);
+            limo3_slopes4(Qm, W0, W1, rz[z0 + 2], lo_0, Sz0);
+            face_flux_s<R>(2, Qm, W0, Szm, lo_0, centre_of(Qm), C0, hpz[z0 + 1], hmz[z0 + 2], Tm + T0, Fz0, recon,
+                           riemann);
         } else {
-            slopes4(Q0, W[0], W[1], wz[z0 + 1], wz[z0 + 2], Szm);
-            slopes4(W[0], W[1], W[2], wz[z0 + 2], wz[z0 + 3], Sz0);
-            face_flux_s<R>(2, W[0], W[1], Szm, Sz0, centre_of(W[0]), C1, hpz[z0 + 1], hmz[z0 + 2], Tm + T1,
-                           a.c_hat, Fzlo, recon, riemann);
+            slopes4(Q0, Qm, W0, rz[z0 + 1], Szm);
+            slopes4(Qm, W0, W1, rz[z0 + 2], Sz0);
+            face_flux_s<R>(2, Qm, W0, Szm, Sz0, centre_of(Qm), C0, hpz[z0 + 1], hmz[z0 + 2], Tm + T0, Fz0, recon,
+                           riemann);
         }
     }
 
@@ -532,42 +543,41 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     // alternation did not pay (1-6 % slower).
     constexpr bool ALTERNATE = !GENERAL;
     const int prio_grp = (int(blockIdx.x) / cus) & 1;
-    for (int k = z0; k < z1; ++k) {
+    // One plane: Wa, Wb are planes k and k + 1 of the window, Wc takes k + 2;
+    // Fa, Fb the fluxes below and above, Sa, Sb the (upper-face) z slopes of
+    // planes k and k + 1.
+    auto step = [&](int k, const R (&Wa)[4], const R (&Wb)[4], R (&Wc)[4], const R (&Fa)[4], R (&Fb)[4],
+                    const R (&Sa)[4], R (&Sb)[4], const Centre<R> &Ca, Centre<R> &Cb, R Ta, R Tb, R &Tc) {
         if constexpr (ALTERNATE) {
             if (((k - z0) ^ prio_grp) & 1)
                 __builtin_amdgcn_s_setprio(1);
             else
                 __builtin_amdgcn_s_setprio(0);
         }
-        // the plane entering the window and this plane's halo
-        load4(a, zlin(k + 2, col), W[3]);
-        fix_col(k + 2, W[3]);
-        T2 = a.tau[zlin(k + 1, col)];
-        R Hq[4], Ht = R(0);
-        if (tid < NHALO) {
-            load4(a, k * plane + hcol, Hq);
-            fix_halo(Hq);
-            Ht = a.tau[k * plane + hcol];
-        }
+        // the plane entering the window
+        loadp(k + 2, col, Wc, Tc);
+        fix_col(k + 2, Wc);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sq[v][ly + 2][lx + 2] = W[1][v];
-        st[ly + 2][lx + 2] = T1;
-        scf[0][ly + 2][lx + 2] = C1.f2;
-        scf[1][ly + 2][lx + 2] = C1.ie;
+        for (int v = 0; v < 4; ++v) sq[v][ly + 2][lx + 2] = Wa[v];
+        st[ly + 2][lx + 2] = Ta;
+        scf[0][ly + 2][lx + 2] = Ca.f2;
+        scf[1][ly + 2][lx + 2] = Ca.ie;
         if (tid < NHALO) {
+            fix_halo(Hq);
 #pragma unroll
             for (int v = 0; v < 4; ++v) sq[v][hy][hx] = Hq[v];
             st[hy][hx] = Ht;
             const Centre<R> ch = centre_of(Hq);
             scf[0][hy][hx] = ch.f2;
             scf[1][hy][hx] = ch.ie;
+            if (k + 1 < z1) loadp(k + 1, hcol, Hq, Ht);
         }
         __syncthreads();
 
         // slopes of the x and y donor cells
 #pragma unroll
         for (int p = 0; p < NSP; ++p) {
-            if (!s_on[p]) continue;
+            if (p == 2 && !s_on) continue;
             R qm[4], q0[4], qp[4], sl[4];
             const int str = p == 0 ? 1 : (p == 1 ? HX : s_str[p]);
             const int ctr = p == 1 ? own + HX + 2 : s_ctr[p];
@@ -580,28 +590,28 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             }
             if constexpr (LIMO3) {
                 R lo[4];
-                limo3_slopes4(qm, q0, qp, s_wl[p], s_wr[p], lo, sl);
+                limo3_slopes4(qm, q0, qp, s_rat[p], lo, sl);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) ssl[v][slot] = lo[v];
             } else {
-                slopes4(qm, q0, qp, s_wl[p], s_wr[p], sl);
+                slopes4(qm, q0, qp, s_rat[p], sl);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) ss[v][slot] = sl[v];
         }
-        // z slope(s) of plane k+1 (LimO3: Sz1 its upper-face slope, Sz1l
-        // its lower-face one)
-        R Sz1[4], Sz1l[4];
+        // z slope(s) of plane k+1 (LimO3: Sb its upper-face slope, Sl its
+        // lower-face one)
+        R Sl[4];
         if constexpr (LIMO3)
-            limo3_slopes4(W[1], W[2], W[3], wz[k + 3], wz[k + 4], Sz1l, Sz1);
+            limo3_slopes4(Wa, Wb, Wc, rz[k + 3], Sl, Sb);
         else
-            slopes4(W[1], W[2], W[3], wz[k + 3], wz[k + 4], Sz1);
+            slopes4(Wa, Wb, Wc, rz[k + 3], Sb);
         __syncthreads();
 
         // x faces (left face of column f) and y faces (lower face of row g)
 #pragma unroll
         for (int p = 0; p < NFP; ++p) {
-            if (!f_on[p]) continue;
+            if (p == 2 && !f_on) continue;
             const int d = p < 2 ? p : f_d[p];
             const int b = p == 1 ? own + HX + 2 : f_b[p], sb = p == 1 ? NXS + tid : f_sb[p];
             const int fo = p < 2 ? tid : f_o[p];
@@ -615,16 +625,15 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
                 slc[v] = LIMO3 ? ssl[v][sb + sst] : ss[v][sb + sst];
             }
             face_flux_s<R>(d, qb, qc, slb, slc, Centre<R>{scf2[b], scie[b]}, Centre<R>{scf2[b + qst], scie[b + qst]},
-                           f_hp[p], f_hm[p], stf[b] + stf[b + qst], a.c_hat, fl, recon, riemann);
+                           f_hp[p], f_hm[p], stf[b] + stf[b + qst], fl, recon, riemann);
             R *dst = d ? &sfy[0][0][0] : &sfx[0][0][0];
             const int fs = d ? (TY + 1) * TX : TY * (TX + 1);
 #pragma unroll
             for (int v = 0; v < 4; ++v) dst[v * fs + fo] = fl[v];
         }
         // z face above the plane from the register window
-        const Centre<R> C2 = centre_of(W[2]);
-        face_flux_s<R>(2, W[1], W[2], Sz0, LIMO3 ? Sz1l : Sz1, C1, C2, hpz[k + 2], hmz[k + 3], T1 + T2, a.c_hat,
-                       Fzhi, recon, riemann);
+        Cb = centre_of(Wb);
+        face_flux_s<R>(2, Wa, Wb, Sa, LIMO3 ? Sl : Sb, Ca, Cb, hpz[k + 2], hmz[k + 3], Ta + Tb, Fb, recon, riemann);
         __syncthreads();
 
         if (live) {
@@ -634,19 +643,23 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
             for (int v = 0; v < 4; ++v)
                 acc[v] = face_diff<same_area<GEOM, 0>>(axl, axh, sfx[v][ly][lx], sfx[v][ly][lx + 1]) +
                          face_diff<same_area<GEOM, 1>>(ayl, ayh, sfy[v][ly][lx], sfy[v][ly + 1][lx]) +
-                         face_diff<same_area<GEOM, 2>>(azl, azh, Fzlo[v], Fzhi[v]);
-            finish_cell<R, GEOM>(a, W[1], C1, acc, ir, ct, (k * n1 + j) * n0 + i);
+                         face_diff<same_area<GEOM, 2>>(azl, azh, Fa[v], Fb[v]);
+            finish_cell<R, GEOM>(a, Wa, Ca, acc, ir, ct, (k * n1 + j) * n0 + i);
         }
+    };
+    for (int k = z0; k < z1; ++k) {
+        R Wn[4], Tn;
+        step(k, W0, W1, Wn, Fz0, Fz1, Sz0, Sz1, C0, C1, T0, T1, Tn);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            Fzlo[v] = Fzhi[v];
+            Fz0[v] = Fz1[v];
             Sz0[v] = Sz1[v];
-            W[0][v] = W[1][v];
-            W[1][v] = W[2][v];
-            W[2][v] = W[3][v];
+            W0[v] = W1[v];
+            W1[v] = Wn[v];
         }
-        T1 = T2;
-        C1 = C2;
+        C0 = C1;
+        T0 = T1;
+        T1 = Tn;
     }
 }
 
