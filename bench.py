@@ -187,8 +187,8 @@ def source_hash(kernel):
     """sha256 of the translation unit a kernel is built from (and its headers)."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_2606_26268_amd", "csrc")
-    files = {"transport": ["transport.hip", "m1_device.h"],
-             "implicit": ["implicit.hip", "opacity_device.h", "mlp_device.h"]}[kernel]
+    files = {"transport": ["transport.hip", "transport_tile.h", "m1_device.h"],
+             "implicit": ["implicit.hip", "implicit_device.h", "opacity_device.h", "mlp_device.h"]}[kernel]
     h = hashlib.sha256()
     for f in files:
         h.update(open(os.path.join(csrc, f), "rb").read())

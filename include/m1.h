@@ -382,8 +382,8 @@ m1_status m1_step_rk2(m1_ctx *ctx, double dt);
 
 /* Device pointers of the library's transported state E*, Fx*, Fy*, Fz*
  * (the state between the explicit and the implicit part of the Sect. 2.4
- * step list; valid after m1_step_explicit; owned by the library).  Gray states only
- * (M1_ENOTSUP with groups). */
+ * step list; valid after m1_step_explicit; owned by the library;
+ * m1_step_rk2 may not store it).  Gray states only (M1_ENOTSUP with groups). */
 m1_status m1_transported(m1_ctx *ctx, void **E, void **Fx, void **Fy, void **Fz);
 
 /* Re-evaluate the opacity cache (rho kappa_P and the optical depth of the

@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libm1.so")
-SOURCES = ["m1_api.hip", "transport.hip", "implicit.hip", "diag.hip", "mlp.hip"]
+SOURCES = ["m1_api.hip", "transport.hip", "stage.hip", "implicit.hip", "diag.hip", "mlp.hip"]
 ARCH = os.environ.get("M1_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -818,6 +818,14 @@ m1_status m1_step_rk2(m1_ctx *c, double dt)
     // U1 = S(T(U^n)) into the save buffer (the caller's arrays keep U^n),
     // then U2 = S(T(U1)) written directly as (U^n + U2) / 2, the opacity
     // cache following each stage's written state
+    // each stage's transport and implicit step in one kernel where that serves
+    if (fused_stages(c)) {
+        hipError_t e = launch_stage(c, dt, 1);
+        if (e == hipSuccess) e = launch_stage(c, dt, 2);
+        if (e != hipSuccess) return hip_fail(e, "m1_step_rk2 stage");
+        c->transported = false;
+        return M1_OK;
+    }
     unsigned char *sv = static_cast<unsigned char *>(c->rk2_save);
     const void *u1[4] = {sv, sv + per, sv + 2 * per, sv + 3 * per};
     hipError_t e = launch_transport(c, dt);

@@ -64,6 +64,19 @@ template <> struct Num<float> {
     static __device__ __forceinline__ float rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 };
 
+// The kernel's first argument, read anew from the argument segment at each
+// use (scalar loads) through a pointer the compiler cannot follow back to the
+// kernel's entry.  For arguments that a march uses in a small part of each
+// plane: hoisted out of it, a large argument's pointers and constants exceed
+// the scalar registers and are kept in vector lanes or scratch.
+template <typename T>
+__device__ __forceinline__ const T &first_argument()
+{
+    auto p = reinterpret_cast<__UINTPTR_TYPE__>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm("" : "+s"(p));
+    return *(const T *)(const __attribute__((address_space(4))) T *)p;
+}
+
 // Adds to counter `which` the number of active lanes of the wavefront with
 // hit set, by one atomic from the lowest such lane into the wavefront's slot
 // of the counter (every active lane calls it).  Fix-up counters see up to
