@@ -15,18 +15,17 @@
 // What bounds it: vector issue in 3D (transport and solve are about 800 FP32
 // operations a cell and stage), where the split step alternated between an
 // issue-bound and a memory-bound kernel.  A second-order step, split -> fused:
-// 256^3 FP32 1363 -> 1024 us, 128^3 FP32 166 -> 113 us and FP64 304 -> 235 us,
-// 192x96x192 FP32 298 -> 240 us (constant opacities), 128^3 FP64 power law 337 ->
-// 324 us, 2D 1000^2 FP64 187 -> 158 us, 1D 2000 cells 17.3 -> 13.8 us.
+// 256^3 FP32 1363 -> 1024 us, 128^3 FP32 166 -> 113 us and FP64 304 -> 220 us,
+// 192x96x192 FP32 298 -> 240 us (constant opacities) and 310 -> 286 us (table),
+// 128^3 FP32 power law 185 -> 151 us, 2D 1000^2 FP64 187 -> 158 us, 300x200 shell
+// with the table 24.0 -> 19.9 us, 1D 2000 cells 17.3 -> 13.8 us.
 //
-// Covers gray states with constant and power-law opacities, in 1D and 2D with
-// every variant, in 3D with the default scheme.  The split kernels stay for:
-// the table, whose logarithms and exponentials hide behind memory in the split
-// kernel and do not here (192x96x192: 317 us both ways in FP32, 568 -> 577 in
-// FP64); the power law in 3D in FP32 (spills at four waves per SIMD, 182 -> 200
-// us on the 128^3 box at three); the network (a wavefront-wide product with
-// its own registers and LDS); frequency groups (the solve needs every group of
-// a cell); and the general 3D kernels (at the edge of their registers).
+// Covers gray states with constant, power-law and tabulated opacities, in 1D
+// and 2D with every variant, in 3D with the default scheme and, in FP64 with
+// temperature-dependent opacities, up to FUSED_P64_CELLS.  The split kernels
+// stay for the network (a wavefront-wide product with its own registers and
+// LDS), frequency groups (the solve needs every group of a cell) and the
+// general 3D kernels (at the edge of their registers).
 #include "transport_tile.h"
 #include "implicit_device.h"
 
@@ -64,7 +63,10 @@ struct SolveCell {
         if (!CONST_OPAC) {
             const R rho = R(in.rho);
             R kP, kR;
-            opacity_analytic<R, OPK_POWERLAW>(ia.op, rho, R(T1), kP, kR);
+            if (ia.op.kind == OPK_POWERLAW)
+                opacity_analytic<R, OPK_POWERLAW>(ia.op, rho, R(T1), kP, kR);
+            else
+                opacity_analytic<R, OPK_TABLE>(ia.op, rho, R(T1), kP, kR);
             cache_entry(rho, kP, kR, R(ia.op.sigma), hm, at(ia.rkp, base, c), at(ia.tau, base, c));
         }
     }
@@ -77,7 +79,7 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<R> a)
 }
 
 template <typename R, int GEOM, int TYB, bool CONST_OPAC>
-__global__ void __launch_bounds__((Tile<TYB>::NT), (sizeof(R) == 4 ? 4 : 2)) k_stage3d(StageArgs<R> a)
+__global__ void __launch_bounds__((Tile<TYB>::NT), (sizeof(R) == 4 ? 4 : (CONST_OPAC ? 3 : 2))) k_stage3d(StageArgs<R> a)
 {
     transport_tile<R, GEOM, false, TYB, false>(a.t, a.nz_chunk, a.tiles_x, a.tiles_y, a.nblocks, a.cus,
                                                SolveCell<R, CONST_OPAC>{});
@@ -100,10 +102,10 @@ template <typename R, int GEOM, bool CONST_OPAC>
 static void launch_geom(m1_ctx *c, StageArgs<R> &a)
 {
     if (c->ndim == 3) {
-        if constexpr (sizeof(R) == 4 && CONST_OPAC) {
-            if (launch_tile<R, GEOM, 16, true>(c, a, 2)) return;
+        if constexpr (sizeof(R) == 4) {
+            if (launch_tile<R, GEOM, 16, CONST_OPAC>(c, a, 2)) return;
         }
-        if constexpr (sizeof(R) == 8 || CONST_OPAC) launch_tile<R, GEOM, 8, CONST_OPAC>(c, a, 0);
+        launch_tile<R, GEOM, 8, CONST_OPAC>(c, a, 0);
         return;
     }
     const long N = long(c->n[0]) * c->n[1];
@@ -145,11 +147,22 @@ static hipError_t launch_s(m1_ctx *c, double dt, const Metric<R> &met, int stage
     return hipGetLastError();
 }
 
+// Temperature-dependent opacities in 3D in FP64: the logarithms, powers and
+// exponentials (about 250 FP64 operations a cell) hide behind memory in the
+// split implicit kernel and add to the issue-bound fused one, about 5 us per
+// million cells and stage (128^3 power law: split 324 us, fused 334;
+// 192x96x192 table: 538 and 574), against some 2.2 us a stage for the launch
+// the fused stage saves (154,000 cells, power law: split 51.4, fused 47.8): the
+// sides meet near half a million cells.
+constexpr long FUSED_P64_CELLS = 1L << 19;
+
 bool fused_stages(const m1_ctx *c)
 {
-    if (c->grp.m > 1 || (c->op.kind != OPK_CONST && c->op.kind != OPK_POWERLAW)) return false;
+    if (c->grp.m > 1 || c->op.kind == OPK_MLP) return false;
     if (c->ndim < 3) return true;
-    if (c->op.kind == OPK_POWERLAW && c->par.precision == M1_F32) return false;
+    if (c->op.kind != OPK_CONST && c->par.precision == M1_P64 &&
+        long(c->n[0]) * c->n[1] * c->n[2] > FUSED_P64_CELLS)
+        return false;
     bool special = false;
     for (int d = 0; d < 3; ++d)
         for (int s = 0; s < 2; ++s)

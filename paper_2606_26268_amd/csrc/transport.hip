@@ -17,33 +17,37 @@ __global__ void __launch_bounds__(256) k_transport(TArgs<R> a)
     transport_cell<R, NDIM, GEOM>(a, StoreCell<R>{a.out, a.out_fs});
 }
 
-// FP32 instantiations ask for at least four (default) and three (general)
-// waves per SIMD (the second argument of the bound), i.e. at most 128 and
-// 168 VGPRs; the FP64 ones for two (at most 256).
+// FP32 instantiations ask for four waves per SIMD (the second argument of the
+// bound), i.e. at most 128 VGPRs; the FP64 ones for three (default, at most 168)
+// and two (general, at most 256).
 // LIMO3 (general kernel only): each donor cell keeps two slopes per
 // direction, one for its lower and one for its upper face, and takes the
-// 32 x 8 tile in FP64 (the 512-thread block spilled).  FP32 fits three
-// waves per SIMD.  FP64 keeps within 256 registers (the spherical kernel by
-// spilling a few to scratch): one wave per SIMD with accumulation registers
-// instead ran 31 % slower.
+// 32 x 8 tile in FP64 (the 512-thread block spilled).
 //
 // What bounds it: vector issue, in FP32 (about 600 operations a cell and
-// plane, 50 of them transcendental at two slots and a third) and in FP64
-// (about 1000, at the 1.85 GHz or so that FP64 work leaves the clock at).  A
-// step of the 128^3 box went from 99 to 92.9 us (FP32) and 176 to 153.8 us
-// (FP64) with the closure without 1 / |F|^2, the face fix on f^2 and the
-// regrouped Riemann flux of m1_device.h, and on to 88.5 and 143.5 us with one
-// spacing factor per slope, dt c_hat in the area factors, one code block for
-// the first two task passes and the halo loaded a plane ahead; 192x96x192
-// with the table in FP64 330 -> 290 -> 270 us, eight groups on the 128^3 box
-// 536 -> 495 -> 460 us.  Tried and not kept: two or three planes per turn of the
-// loop (no register moves; the FP32 kernels spilled and ran 15 % slower, FP64
-// was equal); scalar bases with a 32-bit lane offset for the plane loads and
-// stores (4 % slower); selects in place of the branches of the face fix and
-// the Riemann flux (equal).
+// plane, 50 of them transcendental at two slots and a third; 70-75 % of the
+// cycles issue, the rest is ramp, tail and barriers) and in FP64 (about 1000,
+// 56 % of the cycles).  A step of the 128^3 box went from 99 to 92.9 us (FP32) and
+// 176 to 153.8 us (FP64) with the closure without 1 / |F|^2, the face fix on
+// f^2 and the regrouped Riemann flux of m1_device.h, on to 88.5 and 143.5 us
+// with one spacing factor per slope, dt c_hat in the area factors, one code
+// block for the first two task passes and the halo loaded a plane ahead, and
+// to 86.5 and 140 us with tasks at fixed offsets of the thread's own cell, the
+// metric and update factors in LDS and the x fluxes in the slopes' place
+// (fewer registers and 13 % less LDS: three waves per SIMD in FP64, four in
+// the general FP32 kernels); 192x96x192 with the table in FP64 330 -> 290 -> 270
+// us and, the last step on another card, 262 -> 251 us; eight groups on the
+// 128^3 box 536 -> 495 -> 460 us and 467 -> 462 us; the transport of the FP32
+// box with a lit and a mirror side 55.4 -> 48.3 us in the last step.  Tried and not kept: two or
+// three planes per turn of the loop (no register moves; the FP32 kernels
+// spilled and ran 15 % slower, FP64 was equal); scalar bases with a 32-bit lane
+// offset for the plane loads and stores (4 % slower); selects in place of the
+// branches of the face fix and the Riemann flux (equal); five waves per SIMD
+// in FP32 (2 % faster on 256^3, 7 % slower on 128^3, a few spills); scheduling
+// barriers between the directions (2 % slower in FP64).
 template <typename R, int GEOM, bool GENERAL, int TYB, bool LIMO3 = false>
 __global__ void __launch_bounds__((Tile<TYB>::NT),
-                                  (sizeof(R) == 4 ? (GENERAL ? 3 : 4) : 2))
+                                  (sizeof(R) == 4 ? 4 : (GENERAL ? 2 : 3)))
     k_transport3d(TArgs<R> a, int nz_chunk, int tiles_x, int tiles_y, int nblocks, int cus)
 {
     select_group(a);
@@ -68,9 +72,8 @@ static bool launch_tile(m1_ctx *c, const TArgs<R> &a, unsigned ngrp, long max_ro
 // rounds of resident blocks (the 192x96x192 and 128^3 grids: 1.5 % faster
 // transport than 32 x 8), else 32 x 8 (on the 256^3 grid and eight groups
 // at 128^3, launches of four to sixteen rounds, the taller blocks were
-// 2-4 % slower).  FP64 takes 32 x 8 everywhere: two of its blocks share a
-// compute unit and alternate priority (1-1.5 % faster than one 32 x 16
-// block per unit, which was 2 % faster than 32 x 8 without alternation).
+// 2-4 % slower).  FP64 takes 32 x 8 everywhere (three blocks share a compute
+// unit; two sharing one beat one 32 x 16 block by 1-1.5 %).
 template <typename R, int GEOM, bool GENERAL, bool LIMO3 = false>
 static void launch_tiled(m1_ctx *c, const TArgs<R> &a, unsigned ngrp)
 {

@@ -171,10 +171,12 @@ __device__ __forceinline__ void ignorable_div(const TArgs<R> &a, const R U[4], C
 }
 
 // U* = U - acc + dt c_hat S_geo(U), acc = dt div(Phi) (the fluxes come in units
-// of c_hat and the area factors carry dt c_hat), then E >= floor and f <= 1
+// of c_hat and the area factors carry dt c_hat; k_ = dt c_hat / r_eff, the same
+// number as dt c_hat times the radius factor of the transverse area factors in
+// both curvilinear geometries), then E >= floor and f <= 1
 // (counted).
 template <typename R, int GEOM>
-__device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Centre<R> cu, const R acc[4], R ir, R ct,
+__device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Centre<R> cu, const R acc[4], R k_, R ct,
                                             R Us[4])
 {
 #pragma unroll
@@ -190,7 +192,6 @@ __device__ __forceinline__ void finish_cell(const TArgs<R> &a, const R U[4], Cen
         R an = R(3) * cu.ie * Num<R>::rcp(R(2) + s);
         if (cu.f2 > R(1)) an *= Num<R>::rcp(cu.f2);
         const R iso = (s - R(1)) * (R(1) / R(3)) * U[0];
-        const R k_ = a.dt * a.c_hat * ir;
         if (GEOM == M1_CYLINDRICAL) {           // (R, phi, z)
             const R Ppp = an * U[2] * U[2] + iso, PRp = an * U[1] * U[2];
             Us[1] += k_ * Ppp;
@@ -266,7 +267,7 @@ __device__ __forceinline__ void transport_cell(const TArgs<R> &a, const Fin &fin
     if (a.ign[2]) ignorable_div<R, 2>(a, U, c0, a.m.trA[2][i] * a.m.trB[2][j] * dtc, acc);
 
     R Us[4];
-    finish_cell<R, GEOM>(a, U, c0, acc, GEOM == M1_CARTESIAN ? R(0) : a.m.inv_reff[i],
+    finish_cell<R, GEOM>(a, U, c0, acc, GEOM == M1_CARTESIAN ? R(0) : a.m.inv_reff[i] * dtc,
                          GEOM == M1_SPHERICAL ? a.m.cot_eff[j] : R(0), Us);
     fin(in, Us, a.tau[id], i, j, 0, base, threadIdx.x);
 }
@@ -282,42 +283,29 @@ __device__ __forceinline__ void transport_cell(const TArgs<R> &a, const Fin &fin
 // slopes (faces of both directions in one flat pass, direction chosen at run
 // time), and the z face above the plane from a per-thread register window
 // of four planes and the z slopes of planes k and k+1; (4) the update.
-// Each thread's slope and face assignments are the same in every plane, so
-// their metric factors are loaded once, before the march.
 // ---------------------------------------------------------------------------
 // Tile of a block: TX x TY cells, one thread per cell, TY = 8 (256 threads)
 // or 16 (512 threads).  The taller tile computes 4 % fewer halo faces and
-// slopes per cell; FP32 blocks of it take 55 KB of LDS (two per CU, four
-// waves per SIMD), FP64 blocks 110 KB (one per CU, the two waves per SIMD
-// their registers allow anyway).  The general FP32 kernel has only the
-// 32 x 8 tile: its 150 VGPRs allow three waves per SIMD only in 256-thread
-// blocks.
+// slopes per cell; FP32 blocks of it take 47 KB of LDS (two per CU, four
+// waves per SIMD).  FP64 and general kernels have only the 32 x 8 tile; an FP64
+// block takes 52.6 KB, and three share a CU (LDS is dealt out in steps of 1280
+// bytes, so a block may take 53,760).
 template <int TY_>
 struct Tile {
     static constexpr int TX = 32, TY = TY_, HX = TX + 4, HY = TY + 4, NT = TX * TY;
-    static constexpr int NXF = TY * (TX + 1), NYF = (TY + 1) * TX, NHALO = 2 * (2 * TY + 2 * TX);
-    static constexpr int NXS = TY * (TX + 2), NYS = (TY + 2) * TX;
-    // Task passes of the slope and face stages: pass 0 takes x tasks
-    // 0 .. NT-1, pass 1 y tasks 0 .. NT-1, pass 2 the rest of both (x first),
-    // so that the first two passes run with their direction fixed at compile
-    // time.
-    static_assert(NXF >= NT && NYF >= NT && NXS >= NT && NYS >= NT, "tile too small for the task passes");
-    static_assert(NXF + NYF <= 3 * NT && NXS + NYS <= 3 * NT, "tile too large for three task passes");
-    static_assert(NHALO <= NT, "one halo cell per thread at most");
+    static constexpr int NHALO = 2 * (2 * TY + 2 * TX);
+    // x slots (slopes of the cells of columns -1 .. TX; later x fluxes) and y
+    // slots (slopes of the cells of rows -1 .. TY), each row by row
+    static constexpr int XS = TX + 2, NXS = TY * XS, NYS = (TY + 2) * TX;
+    // Task passes of the slope and face stages: in pass 0 thread (lx, ly) takes
+    // the slope of column lx - 1 and the face left of column lx, in pass 1 the
+    // slope of row ly - 1 and the face below row ly (their direction is fixed
+    // at compile time); pass 2 takes what is left, x first: the slopes of two
+    // columns and two rows, the faces right of the last column and above the
+    // last row.
+    static constexpr int S2X = 2 * TY, S2 = S2X + 2 * TX, F2X = TY, F2 = F2X + TX;
+    static_assert(S2 <= NT && F2 <= NT && NHALO <= NT, "one task per thread in pass 2, one halo cell at most");
 };
-constexpr int NSP = 3, NFP = 3;
-
-// task of thread tid in pass p: direction (0 = x, 1 = y) and index within
-// that direction's tasks, or -1 past the last (nx, ny: task counts)
-template <int NT>
-__device__ __forceinline__ int task_of(int p, int tid, int nx, int ny, int &dir)
-{
-    dir = p == 1 ? 1 : 0;
-    if (p < 2) return tid;
-    if (tid < nx - NT) return NT + tid;
-    dir = 1;
-    return tid - (nx - NT) < ny - NT ? NT + tid - (nx - NT) : -1;
-}
 
 template <typename R, int GEOM, bool GENERAL, int TYB, bool LIMO3, class Fin>
 __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, int tiles_x, int tiles_y, int nblocks,
@@ -325,22 +313,34 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
 {
     using T = Tile<TYB>;
     constexpr int TX = T::TX, TY = T::TY, HX = T::HX, HY = T::HY, NT = T::NT;
-    constexpr int NXF = T::NXF, NYF = T::NYF, NHALO = T::NHALO, NXS = T::NXS, NYS = T::NYS;
+    constexpr int NHALO = T::NHALO, XS = T::XS, NXS = T::NXS, NYS = T::NYS;
     // the default scheme (f-preserving fix + HLL, periodic / outflow sides)
     // is compiled without the variant and ghost-state code
     const int recon = GENERAL ? a.recon : int(M1_RECON_FPRESERVE);
     const int riemann = GENERAL ? a.riemann : int(M1_RIEMANN_HLL);
     __shared__ R sq[4][HY][HX];
-    __shared__ R st[HY][HX];
-    __shared__ R scf[2][HY][HX];        // |F|^2 and 1 / E of the staged cells
+    // optical depth, f^2 and 1 / E of the staged cells a face can have as a
+    // donor: rows -1 .. TY (the outermost rows only enter slopes)
+    __shared__ R st[HY - 2][HX];
+    __shared__ R scf[2][HY - 2][HX];
     static_assert(GENERAL || !LIMO3, "LimO3 only in the general kernel");
-    __shared__ R ss[4][NXS + NYS];      // slopes: x tasks, then y tasks (LimO3: upper-face slopes)
+    // Slopes, x slots then y slots (LimO3: upper-face slopes).  The x fluxes
+    // take the place of the x slopes: the face left of column c is computed by
+    // the wavefront that owns its row, which has read every slope of the row
+    // but the last two by then, and goes to the slot of column c - 1; the face
+    // right of the last column reads the last two slots and goes to the last,
+    // which only it reads.
+    __shared__ R ss[4][NXS + NYS];
     __shared__ R ssl[LIMO3 ? 4 : 1][LIMO3 ? NXS + NYS : 1];   // LimO3: lower-face slopes
-    __shared__ R sfx[4][TY][TX + 1];
     __shared__ R sfy[4][TY + 1][TX];
+    // spacing ratio and the two centre-to-face offsets of the cells of columns
+    // -1 .. TX and rows -1 .. TY
+    __shared__ R smx[3][TX + 2], smy[3][TY + 2];
+    __shared__ R sux[3][TX], suy[GEOM == M1_SPHERICAL ? 4 : 2][TY];
     R *const sqf = &sq[0][0][0];
-    const R *const stf = &st[0][0];
-    const R *const scf2 = &scf[0][0][0], *const scie = &scf[1][0][0];
+    // of the cell at flat index b of sq
+    const auto depth = [&](int b) { return (&st[0][0])[b - HX]; };
+    const auto centre = [&](int b) { return Centre<R>{(&scf[0][0][0])[b - HX], (&scf[1][0][0])[b - HX]}; };
     constexpr int QS = HY * HX;
 
     // consecutive logical tiles share an XCD (blocks are dealt to XCDs round-robin)
@@ -359,7 +359,8 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     const int plane = n0 * n1;
     const int col = mj * n0 + mi;
 
-    // halo cell of this thread (tid < NHALO): cross-shaped, no corners
+    // halo cell of this thread (tid < NHALO): cross-shaped, no corners; its
+    // index in sq, and whether it is also in st and scf
     int hx = 0, hy = 0, hcol = 0;
     if (tid < NHALO) {
         if (tid < 2 * TX) { hy = tid / TX; hx = 2 + tid % TX; }
@@ -370,6 +371,8 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         const int gj = map_index(y0 - 2 + hy, n1, a.bc[1][0], a.bc[1][1]);
         hcol = gj * n0 + gi;
     }
+    const int hq = hy * HX + hx;
+    const bool donor = tid >= TX && (tid < 3 * TX || tid >= 4 * TX);
     // ghost transformation of a state in this thread's column (x, y ghosts)
     // and in plane kk (z ghosts); halo cells are ghosts in x or y only
     auto fix_col = [&](int kk, R q[4]) {
@@ -386,94 +389,56 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         ghost_fix(g, 1, y0 - 2 + hy, n1, q);
     };
 
-    // Passes 0 and 1 take the tasks numbered like the threads, so their flux
-    // and slope slots are the thread's index and the y tasks' cells lie at a
-    // fixed offset from the thread's own: those words are immediate offsets
-    // of one address and are not kept (6 registers fewer).
-    const int own = ly * HX + lx;
-    // slope tasks: centre cell in sq (flat), neighbour stride, spacing ratio.
-    // Cells past the last ghost (m > n) feed no face that is used: passes 0
-    // and 1 run them along (on staged cells and a zero ratio) rather than
-    // split the code into one block per pass, pass 2 is left to the
-    // wavefronts that have tasks in it.
-    int s_ctr[NSP], s_str[NSP], s_slot[NSP];
-    R s_rat[NSP];
-    bool s_on = false;
-#pragma unroll
-    for (int p = 0; p < NSP; ++p) {
-        int dir;
-        s_on = false;                   // the last pass decides
-        const int q = task_of<NT>(p, tid, NXS, NYS, dir);
-        s_ctr[p] = 2 * HX + 2;
-        s_str[p] = 1;
-        s_rat[p] = R(0);
-        if (q >= 0 && dir == 0) {
-            const int r = q / (TX + 2), c = q % (TX + 2), m = x0 + c - 1;
-            if (m <= n0) {
-                s_on = true;
-                s_ctr[p] = (r + 2) * HX + c + 1;
-                s_rat[p] = a.m.rat[0][m + 2];
-            }
-        } else if (q >= 0) {
-            const int qq = q, r = qq / TX, c = qq % TX, m = y0 + r - 1;
-            if (m <= n1) {
-                s_on = true;
-                s_ctr[p] = (r + 1) * HX + c + 2;
-                s_str[p] = HX;
-                s_rat[p] = a.m.rat[1][m + 2];
-            }
-        }
-        s_slot[p] = dir == 0 ? q : NXS + q;
+    // Every task's cells and slots lie at fixed offsets from the thread's own
+    // cell in passes 0 and 1, so one address serves them all.  Cells past the
+    // last ghost feed no face that is used: passes 0 and 1 run them along (on
+    // staged cells and a zero ratio) rather than split the code into one block
+    // per pass, pass 2 is left to the wavefronts that have tasks in it.
+    const int own = ly * HX + lx, xs = ly * XS + lx;
+    const bool s_on = tid < T::S2, f_on = tid < T::F2;
+    // The thread's index as pass 2 decodes it: FP64 and LimO3 kernels hide it
+    // from the compiler, which otherwise keeps the decoded words through the
+    // march (10 registers: the third wave per SIMD in FP64, the fourth in FP32
+    // with LimO3; the other kernels have them to spare and are 2-3 % faster with
+    // the words kept).
+    const auto task = [&] {
+        int t = tid;
+        if constexpr (sizeof(R) == 8 ? !GENERAL : LIMO3) asm("" : "+v"(t));
+        return t;
+    };
+    // metric of the tile's columns and rows (read after the first barrier)
+    if (tid < TX + 2) {
+        const int m = x0 + tid - 1;
+        smx[0][tid] = m <= n0 ? a.m.rat[0][m + 2] : R(0);
+        smx[1][tid] = m <= n0 ? a.m.hp[0][m + 2] : R(0);
+        smx[2][tid] = m <= n0 ? a.m.hm[0][m + 2] : R(0);
+    } else if (tid >= 64 && tid < 64 + TY + 2) {
+        const int q = tid - 64, m = y0 + q - 1;
+        smy[0][q] = m <= n1 ? a.m.rat[1][m + 2] : R(0);
+        smy[1][q] = m <= n1 ? a.m.hp[1][m + 2] : R(0);
+        smy[2][q] = m <= n1 ? a.m.hm[1][m + 2] : R(0);
     }
-    // face tasks: direction, left donor in sq, its slope in ss, flux slot,
-    // centre-to-face offsets of the two donors
-    int f_d[NFP], f_b[NFP], f_sb[NFP], f_o[NFP];
-    R f_hp[NFP], f_hm[NFP];
-    bool f_on = false;
-#pragma unroll
-    for (int p = 0; p < NFP; ++p) {
-        int dir;
-        f_on = false;
-        const int q = task_of<NT>(p, tid, NXF, NYF, dir);
-        f_d[p] = 0;
-        f_b[p] = f_sb[p] = f_o[p] = 0;
-        f_hp[p] = f_hm[p] = R(0);
-        if (q >= 0 && dir == 0) {
-            const int row = q / (TX + 1), fo = q % (TX + 1), g = x0 + fo;
-            if (g <= n0 && y0 + row < n1) {
-                f_on = true;
-                f_b[p] = (row + 2) * HX + fo + 1;
-                f_sb[p] = row * (TX + 2) + fo;
-                f_o[p] = row * (TX + 1) + fo;
-                f_hp[p] = a.m.hp[0][g + 1];
-                f_hm[p] = a.m.hm[0][g + 2];
-            }
-        } else if (q >= 0) {
-            const int qq = q, go = qq / TX, cl = qq % TX, g = y0 + go;
-            if (g <= n1 && x0 + cl < n0) {
-                f_on = true;
-                f_d[p] = 1;
-                f_b[p] = (go + 1) * HX + cl + 2;
-                f_sb[p] = NXS + go * TX + cl;
-                f_o[p] = go * TX + cl;
-                f_hp[p] = a.m.hp[1][g + 1];
-                f_hm[p] = a.m.hm[1][g + 2];
-            }
+    // Update factors of the tile's columns (the area factors of x, dt c_hat
+    // among them, and the radius factor of the other directions, which is also
+    // that of the geometric sources) and rows (the area factors of y, the sine
+    // factor of z and cot theta).
+    if (tid >= 128 && tid < 128 + TX) {
+        const int c = tid - 128, m = x0 + c;
+        const R dtc = m < n0 ? a.dt * a.c_hat : R(0);
+        const int mm = min(m, n0 - 1);
+        sux[0][c] = a.m.alo[0][mm] * dtc;
+        sux[1][c] = a.m.ahi[0][mm] * dtc;
+        sux[2][c] = a.m.trA[1][mm] * dtc;
+    } else if (tid >= 192 && tid < 192 + TY) {
+        const int q = tid - 192, mm = min(y0 + q, n1 - 1);
+        suy[0][q] = a.m.alo[1][mm];
+        suy[1][q] = a.m.ahi[1][mm];
+        if (GEOM == M1_SPHERICAL) {
+            suy[2][q] = a.m.trB[2][mm];
+            suy[3][q] = a.m.cot_eff[mm];
         }
     }
-    // update factors of the thread's column, dt c_hat among them
-    R axl = R(0), axh = R(0), ayl = R(0), ayh = R(0), tr2 = R(0), ir = R(0), ct = R(0);
-    if (live) {
-        const R dtc = a.dt * a.c_hat;
-        axl = a.m.alo[0][i] * dtc;
-        axh = a.m.ahi[0][i] * dtc;
-        const R tr1 = a.m.trA[1][i] * dtc;
-        ayl = a.m.alo[1][j] * tr1;
-        ayh = a.m.ahi[1][j] * tr1;
-        tr2 = a.m.trA[2][i] * a.m.trB[2][j] * dtc;
-        if (GEOM != M1_CARTESIAN) ir = a.m.inv_reff[i];
-        if (GEOM == M1_SPHERICAL) ct = a.m.cot_eff[j];
-    }
+    const R dtc = a.dt * a.c_hat;
 
     const int bz0 = a.bc[2][0], bz1 = a.bc[2][1];
     // cell c of plane kk (mapped) and its optical depth
@@ -553,29 +518,49 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         fix_col(k + 2, Wc);
 #pragma unroll
         for (int v = 0; v < 4; ++v) sq[v][ly + 2][lx + 2] = Wa[v];
-        st[ly + 2][lx + 2] = Ta;
-        scf[0][ly + 2][lx + 2] = Ca.f2;
-        scf[1][ly + 2][lx + 2] = Ca.ie;
+        st[ly + 1][lx + 2] = Ta;
+        scf[0][ly + 1][lx + 2] = Ca.f2;
+        scf[1][ly + 1][lx + 2] = Ca.ie;
         if (tid < NHALO) {
             fix_halo(Hq);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sq[v][hy][hx] = Hq[v];
-            st[hy][hx] = Ht;
-            const Centre<R> ch = centre_of(Hq);
-            scf[0][hy][hx] = ch.f2;
-            scf[1][hy][hx] = ch.ie;
+            for (int v = 0; v < 4; ++v) sqf[v * QS + hq] = Hq[v];
+            if (donor) {
+                (&st[0][0])[hq - HX] = Ht;
+                const Centre<R> ch = centre_of(Hq);
+                (&scf[0][0][0])[hq - HX] = ch.f2;
+                (&scf[1][0][0])[hq - HX] = ch.ie;
+            }
             if (k + 1 < z1) loadp(k + 1, hcol, Hq, Ht);
         }
         __syncthreads();
 
         // slopes of the x and y donor cells
 #pragma unroll
-        for (int p = 0; p < NSP; ++p) {
+        for (int p = 0; p < 3; ++p) {
             if (p == 2 && !s_on) continue;
-            R qm[4], q0[4], qp[4], sl[4];
-            const int str = p == 0 ? 1 : (p == 1 ? HX : s_str[p]);
-            const int ctr = p == 1 ? own + HX + 2 : s_ctr[p];
-            const int slot = p == 0 ? tid : (p == 1 ? NXS + tid : s_slot[p]);
+
+            R qm[4], q0[4], qp[4], sl[4], rat;
+            bool y = p == 1;
+            int ctr, slot;                  // centre cell and slope slot
+            if (p == 0) {
+                ctr = own + 2 * HX + 1;
+                slot = xs;
+                rat = smx[0][lx];
+            } else if (p == 1) {
+                ctr = own + HX + 2;
+                slot = NXS + tid;
+                rat = smy[0][ly];
+            } else {
+                const int t2 = task();
+                y = t2 >= T::S2X;
+                const int q = t2 - T::S2X;
+                const int r = y ? TY + q / TX : t2 >> 1, c = y ? q % TX : TX + (t2 & 1);
+                ctr = (r + (y ? 1 : 2)) * HX + c + (y ? 2 : 1);
+                slot = y ? NXS + r * TX + c : r * XS + c;
+                rat = y ? smy[0][r] : smx[0][c];
+            }
+            const int str = y ? HX : 1;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 qm[v] = sqf[v * QS + ctr - str];
@@ -584,15 +569,16 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
             }
             if constexpr (LIMO3) {
                 R lo[4];
-                limo3_slopes4(qm, q0, qp, s_rat[p], lo, sl);
+                limo3_slopes4(qm, q0, qp, rat, lo, sl);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) ssl[v][slot] = lo[v];
             } else {
-                slopes4(qm, q0, qp, s_rat[p], sl);
+                slopes4(qm, q0, qp, rat, sl);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) ss[v][slot] = sl[v];
         }
+
         // z slope(s) of plane k+1 (LimO3: Sb its upper-face slope, Sl its
         // lower-face one)
         R Sl[4];
@@ -602,14 +588,36 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
             slopes4(Wa, Wb, Wc, rz[k + 3], Sb);
         __syncthreads();
 
-        // x faces (left face of column f) and y faces (lower face of row g)
+        // x faces (left face of a column) and y faces (lower face of a row)
 #pragma unroll
-        for (int p = 0; p < NFP; ++p) {
+        for (int p = 0; p < 3; ++p) {
             if (p == 2 && !f_on) continue;
-            const int d = p < 2 ? p : f_d[p];
-            const int b = p == 1 ? own + HX + 2 : f_b[p], sb = p == 1 ? NXS + tid : f_sb[p];
-            const int fo = p < 2 ? tid : f_o[p];
-            const int qst = d ? HX : 1, sst = d ? TX : 1;
+
+            bool y = p == 1;
+            int b, sb, fo;                  // left donor, its slope's slot, flux slot
+            R hp, hm;
+            if (p == 0) {
+                b = own + 2 * HX + 1;
+                sb = fo = xs;
+                hp = smx[1][lx];
+                hm = smx[2][lx + 1];
+            } else if (p == 1) {
+                b = own + HX + 2;
+                sb = NXS + tid;
+                fo = tid;
+                hp = smy[1][ly];
+                hm = smy[2][ly + 1];
+            } else {
+                const int t2 = task();
+                y = t2 >= T::F2X;
+                const int c = t2 - T::F2X;
+                b = y ? (TY + 1) * HX + c + 2 : (t2 + 2) * HX + TX + 1;
+                sb = y ? NXS + TY * TX + c : t2 * XS + TX;
+                fo = y ? NT + c : sb + 1;
+                hp = y ? smy[1][TY] : smx[1][TX];
+                hm = y ? smy[2][TY + 1] : smx[2][TX + 1];
+            }
+            const int qst = y ? HX : 1, sst = y ? TX : 1;
             R qb[4], qc[4], slb[4], slc[4], fl[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -618,13 +626,14 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
                 slb[v] = ss[v][sb];
                 slc[v] = LIMO3 ? ssl[v][sb + sst] : ss[v][sb + sst];
             }
-            face_flux_s<R>(d, qb, qc, slb, slc, Centre<R>{scf2[b], scie[b]}, Centre<R>{scf2[b + qst], scie[b + qst]},
-                           f_hp[p], f_hm[p], stf[b] + stf[b + qst], fl, recon, riemann);
-            R *dst = d ? &sfy[0][0][0] : &sfx[0][0][0];
-            const int fs = d ? (TY + 1) * TX : TY * (TX + 1);
+            face_flux_s<R>(p == 2 ? int(y) : p, qb, qc, slb, slc, centre(b), centre(b + qst), hp, hm,
+                           depth(b) + depth(b + qst), fl, recon, riemann);
+            R *dst = y ? &sfy[0][0][0] : &ss[0][0];
+            const int fs = y ? (TY + 1) * TX : NXS + NYS;
 #pragma unroll
             for (int v = 0; v < 4; ++v) dst[v * fs + fo] = fl[v];
         }
+
         // z face above the plane from the register window
         Cb = centre_of(Wb);
         face_flux_s<R>(2, Wa, Wb, Sa, LIMO3 ? Sl : Sb, Ca, Cb, hpz[k + 2], hmz[k + 3], Ta + Tb, Fb, recon, riemann);
@@ -640,13 +649,19 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
 
         if (live) {
             R acc[4], Us[4];
-            const R azl = a.m.alo[2][k] * tr2, azh = a.m.ahi[2][k] * tr2;
+            const int xr = xs + 1 + (lx == TX - 1);      // slot of the flux right of the cell
+            const R axl = sux[0][lx], axh = same_area<GEOM, 0> ? axl : sux[1][lx];
+            const R tr1 = GEOM == M1_CARTESIAN ? dtc : sux[2][lx];
+            const R ayl = suy[0][ly] * tr1, ayh = same_area<GEOM, 1> ? ayl : suy[1][ly] * tr1;
+            const R tr2 = GEOM == M1_SPHERICAL ? suy[2][ly] * tr1 : dtc;
+            const R azl = a.m.alo[2][k] * tr2, azh = same_area<GEOM, 2> ? azl : a.m.ahi[2][k] * tr2;
+            const R ct = GEOM == M1_SPHERICAL ? suy[3][ly] : R(0);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                acc[v] = face_diff<same_area<GEOM, 0>>(axl, axh, sfx[v][ly][lx], sfx[v][ly][lx + 1]) +
+                acc[v] = face_diff<same_area<GEOM, 0>>(axl, axh, ss[v][xs], ss[v][xr]) +
                          face_diff<same_area<GEOM, 1>>(ayl, ayh, sfy[v][ly][lx], sfy[v][ly + 1][lx]) +
                          face_diff<same_area<GEOM, 2>>(azl, azh, Fa[v], Fb[v]);
-            finish_cell<R, GEOM>(a, Wa, Ca, acc, ir, ct, Us);
+            finish_cell<R, GEOM>(a, Wa, Ca, acc, tr1, ct, Us);
             fin(in, Us, Ta, i, j, k, base, cell);
         }
     };

@@ -1,6 +1,6 @@
 """The second-order step where one kernel takes a stage's transport and
-implicit step together (constant and power-law opacities), against the
-oracle: every dimension and geometry, grids that end inside a tile, a wave
+implicit step together (constant, power-law and tabulated opacities), against
+the oracle: every dimension and geometry, grids that end inside a tile, a wave
 or a z chunk, periodic wrap shorter than the stencil, irradiation and
 absorption, the 1D/2D variants, and its place in a run beside the split
 steps (the power law's optical depths change hands between the stages)."""
@@ -70,10 +70,11 @@ def _check(orc, p, precision, steps, label, split=False):
     (I.CARTESIAN, (257, 1, 1), 1), (I.SPHERICAL, (50, 1, 1), 1), (I.CARTESIAN, (37, 23, 1), 2),
     (I.CYLINDRICAL, (29, 17, 1), 2), (I.CARTESIAN, (33, 17, 18), 3), (I.CARTESIAN, (5, 9, 1), 3),
     (I.CYLINDRICAL, (21, 13, 11), 3), (I.SPHERICAL, (64, 16, 3), 3)])
-@pytest.mark.parametrize("opacity", ["constant", "powerlaw"])
+@pytest.mark.parametrize("opacity", ["constant", "powerlaw", "table"])
 @pytest.mark.parametrize("precision", ["p64", "f32"])
 def test_fused_stages_match_oracle(orc, geom, n, ndim, opacity, precision):
-    p = _problem(geom, n, ndim, CONST if opacity == "constant" else POWER, seed=300 + 7 * geom + ndim)
+    op = {"constant": CONST, "powerlaw": POWER, "table": I.make_table()}[opacity]
+    p = _problem(geom, n, ndim, op, seed=300 + 7 * geom + ndim)
     _check(orc, p, precision, 4, f"stages geom={geom} n={n} ndim={ndim} {opacity}")
 
 
@@ -82,6 +83,12 @@ def test_fused_stages_match_oracle(orc, geom, n, ndim, opacity, precision):
 def test_fused_stages_irradiated_absorbing(orc, n, ndim, opacity):
     p = _problem(I.CARTESIAN, n, ndim, CONST if opacity == "constant" else POWER, seed=17, special=True)
     _check(orc, p, "p64", 4, f"stages irradiated absorbing n={n} {opacity}")
+
+
+def test_split_stages_past_the_cell_limit(orc):
+    """FP64, power law, 3D: just past the cell count up to which stages fuse."""
+    p = _problem(I.CARTESIAN, (89, 80, 74), 3, POWER, seed=5)
+    _check(orc, p, "p64", 1, "stages past the cell limit")
 
 
 @pytest.mark.parametrize("variant", [dict(recon=1, riemann=1), dict(limiter=1)])
