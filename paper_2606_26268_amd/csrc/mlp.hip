@@ -2,11 +2,13 @@
 //
 // Training minimises L = (1/B) sum_b sum_o (y_bo - t_bo)^2 / 2 over
 // mini-batches of table coordinates, targets t = (log10 kappa_table - mean)
-// / std from bilinear lookups of the bound table.  One wavefront handles 64
-// samples: forward as in inference, back-propagation with the two 64x64
-// products (dL/dh1 = W2^T dz2 and dL/dW2 = sum_s dz2 h1^T) on the bfloat16
-// matrix cores with split (hi + lo) operands and FP32 accumulation, the
-// small layers on the vector ALU.  Per-wave gradients go to a partial buffer
+// / std from bilinear lookups of the bound table.  One block handles 64
+// samples: layers 1 and 3 on the vector ALU in FP32, the 64x64 products of the
+// forward pass (W2 h1) and of back-propagation (dL/dh1 = W2^T dz2 and dL/dW2 =
+// sum_s dz2 h1^T) on the bfloat16 matrix cores (v_mfma_f32_32x32x16_bf16, FP32
+// accumulation) with each operand split into a high part and a remainder,
+// keeping hi*hi + hi*lo + lo*hi (about 16 significant bits per product), the
+// small layers on the vector ALU.  Per-block gradients go to a partial buffer
 // that one kernel reduces in a fixed order before the Adam update (Kingma &
 // Ba 2015), so training is deterministic.
 #include <cmath>
@@ -143,7 +145,7 @@ int mlp_pack(m1_ctx *c, const float *theta, const double *norm)
 }
 
 // ---------------------------------------------------------------------------
-// forward + backward of one 64-sample wavefront
+// forward + backward of 64 samples
 // ---------------------------------------------------------------------------
 
 struct TrainArgs {
@@ -156,6 +158,12 @@ struct TrainArgs {
     float *partial;        // [nblk][NP]
     float *loss_part;      // [nblk]
 };
+
+// value of v in a lane given by a wavefront-uniform number
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
 
 __device__ __forceinline__ void split8(const float v[8], bf16x8 &h, bf16x8 &l)
 {
@@ -176,196 +184,239 @@ __device__ __forceinline__ f32x16 mfma3(const bf16x8 &ah, const bf16x8 &al, cons
     return acc;
 }
 
-__global__ void __launch_bounds__(64) k_mlp_fwd_bwd(TrainArgs a)
+// Sums over the 64 samples in their order: of column[s] weight[s] (weights the
+// same in every lane, 16-byte aligned) and of column[s].
+__device__ __forceinline__ float dot64(const float *column, const float *weight)
 {
-    __shared__ float H1[64 * LDS_STRIDE];
-    __shared__ float DZ2[64 * LDS_STRIDE];
-    __shared__ float H2[64 * LDS_STRIDE];   // later reused for dz1
-    __shared__ float XS[64][2];
-    __shared__ float DY[64][2];
-    const int lane = threadIdx.x, g = lane >> 5, l32 = lane & 31;
-    const float *p = a.pk;
+    const float4 *wt = reinterpret_cast<const float4 *>(weight);
+    float acc = 0.f;
+#pragma unroll
+    for (int s = 0; s < 64; s += 4) {
+        const float4 x = wt[s / 4];
+        acc += column[s * LDS_STRIDE] * x.x;
+        acc += column[(s + 1) * LDS_STRIDE] * x.y;
+        acc += column[(s + 2) * LDS_STRIDE] * x.z;
+        acc += column[(s + 3) * LDS_STRIDE] * x.w;
+    }
+    return acc;
+}
 
-    const long sidx = (a.offset + (long)blockIdx.x * 64 + lane) % a.n_train;
+__device__ __forceinline__ float sum64(const float *column)
+{
+    float acc = 0.f;
+#pragma unroll
+    for (int s = 0; s < 64; ++s) acc += column[s * LDS_STRIDE];
+    return acc;
+}
+
+// What bounds it: latency.  A batch is a few dozen to a few hundred blocks, each
+// a chain of small dependent products, so the work of 64 samples is spread over
+// the wavefronts of a block: the first four hold one 32 x 32 tile each of the
+// three 64 x 64 products (and layer 1 of 16 samples each), the fifth the table
+// targets, the loss and the output bias and shortcut, the last three, while the
+// first four multiply, one sum over samples per hidden layer each (the two
+// weights and the bias).  Every sum keeps the order of one lane per parameter.
+// A training step at batch 4096 (64 blocks), one wavefront per 64 samples -> this
+// with the deeper reduction below: 27.3 -> 10.7 us (this kernel 18.3 -> 6.5 us: 13,200
+// cycles, of them 4,400 up to the end of layer 1, most of it the first loads,
+// and 4,100 in the two products of back-propagation); 2368 samples 24.0 -> 11.3 us.
+// A block takes 69 KB of LDS: two per compute unit.
+constexpr int TRAIN_THREADS = 512;
+
+__global__ void __launch_bounds__(TRAIN_THREADS) k_mlp_fwd_bwd(TrainArgs a)
+{
+    __shared__ float H1[64 * LDS_STRIDE], H2[64 * LDS_STRIDE], DZ1[64 * LDS_STRIDE], DZ2[64 * LDS_STRIDE];
+    __shared__ float4 W3q[32];              // W3[2][64]
+    __shared__ float4 DYq[32], X1q[48];     // [2][64] dL/dy and [3][64] x0, x1, 1, by sample
+    __shared__ float PART[2][2][64];        // [output][half of the units][sample]
+    const float *W3 = reinterpret_cast<const float *>(W3q);
+    float *DY = reinterpret_cast<float *>(DYq), *X1 = reinterpret_cast<float *>(X1q);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 5, l32 = lane & 31;
+    const int mt = (w >> 1) & 1, nt = w & 1;   // the wavefront's tile (wavefronts 0..3)
+    const bool tiles = w < 4, head = w == 4;
+    const float *p = a.pk;
+    float *out = a.partial + (long)blockIdx.x * NP;
+
+    // wavefronts 0..3: lane % 16 is the sample within the wavefront's 16;
+    // the others: one sample a lane
+    const int s0 = tiles ? 16 * w + (lane & 15) : lane;
+    long sidx = a.offset + (long)blockIdx.x * 64 + s0;
+    if (sidx >= a.n_train) sidx %= a.n_train;
     const float lr = a.samples[2 * sidx], lt = a.samples[2 * sidx + 1];
     const float x0 = 2.0f * (lr - float(a.op.lr0)) / float(a.op.lr1 - a.op.lr0) - 1.0f;
     const float x1 = 2.0f * (lt - float(a.op.lt0)) / float(a.op.lt1 - a.op.lt0) - 1.0f;
-    double tP, tR;
-    table_lookup<double>(a.op, double(lr), double(lt), tP, tR);
-    const float t0 = float((tP - a.op.norm[0]) / a.op.norm[1]);
-    const float t1 = float((tR - a.op.norm[2]) / a.op.norm[3]);
 
-    MlpWave net;
-    net.load(p, lane);
-    float h1[64];
-    net.layer1(x0, x1, h1);
+    bf16x8 w2h[4], w2l[4], wth[4], wtl[4];   // rows 32 mt.. of W2 and of W2^T
+    float4 b2[4];
+    float b3[2], ws[4];
+    if (tiles) {
 #pragma unroll
-    for (int u = 0; u < 64; ++u) H1[lane * LDS_STRIDE + u] = h1[u];
-    f32x16 acc[2][2];
-    net.layer2(h1, lane, acc);
-    float h2[2][2][16];
-    float part[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+        for (int ks = 0; ks < 4; ++ks) {
+            const int f = (mt * 4 + ks) * 64 + lane;
+            w2h[ks] = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2HI)[f];
+            w2l[ks] = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2LO)[f];
+            wth[ks] = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2THI)[f];
+            wtl[ks] = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2TLO)[f];
+        }
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+        for (int q = 0; q < 4; ++q) b2[q] = *reinterpret_cast<const float4 *>(p + MLP_OFF_B2 + mlp_unit(mt, 4 * q, g));
+        // layer 1: lane = unit
+        const float2 w1 = reinterpret_cast<const float2 *>(p + MLP_OFF_W1)[lane];
+        const float b1 = p[MLP_OFF_B1 + lane];
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int j = 0; j < 16; ++j) {
+            const float y0 = lane_value(x0, j), y1 = lane_value(x1, j);
+            H1[(16 * w + j) * LDS_STRIDE + lane] = fast_tanh(w1.x * y0 + w1.y * y1 + b1);
+        }
+    } else if (head) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int u = MlpWave::unit(mt, i, g);
-                const float h = fast_tanh(acc[mt][nt][i] + p[MLP_OFF_B2 + u]);
-                h2[mt][nt][i] = h;
-                H2[(32 * nt + l32) * LDS_STRIDE + u] = h;
-                part[nt][0] += p[MLP_OFF_W3 + u] * h;
-                part[nt][1] += p[MLP_OFF_W3 + 64 + u] * h;
-            }
-    const float s0 = g ? part[0][0] : part[1][0], s1 = g ? part[0][1] : part[1][1];
-    const float r0 = __shfl_xor(s0, 32), r1 = __shfl_xor(s1, 32);
-    const float y0 = (g ? part[1][0] : part[0][0]) + r0 + p[MLP_OFF_B3] + p[MLP_OFF_WS] * x0 + p[MLP_OFF_WS + 1] * x1;
-    const float y1 = (g ? part[1][1] : part[0][1]) + r1 + p[MLP_OFF_B3 + 1] + p[MLP_OFF_WS + 2] * x0 +
-                     p[MLP_OFF_WS + 3] * x1;
-    const float e0 = y0 - t0, e1 = y1 - t1;
-    float lossl = 0.5f * (e0 * e0 + e1 * e1) * a.inv_batch;
-    XS[lane][0] = x0;
-    XS[lane][1] = x1;
-    DY[lane][0] = e0 * a.inv_batch;
-    DY[lane][1] = e1 * a.inv_batch;
+        for (int q = 0; q < 2; ++q) b3[q] = p[MLP_OFF_B3 + q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ws[q] = p[MLP_OFF_WS + q];
+    } else {
+        if (w == 7 && lane < 32) W3q[lane] = reinterpret_cast<const float4 *>(p + MLP_OFF_W3)[lane];
+        X1[64 * (w - 5) + lane] = w == 5 ? x0 : w == 6 ? x1 : 1.0f;
+    }
     __syncthreads();
 
-    // dz2 = (W3^T dy) * (1 - h2^2), in the matrix-core output layout
+    // layer 2, Z2^T = W2 H1^T
+    float h2[16];
+    float t0 = 0.f, t1 = 0.f;
+    if (tiles) {
+        f32x16 acc;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int s = 32 * nt + l32;
-            const float d0 = DY[s][0], d1 = DY[s][1];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int u = MlpWave::unit(mt, i, g);
-                const float h = h2[mt][nt][i];
-                DZ2[s * LDS_STRIDE + u] = (p[MLP_OFF_W3 + u] * d0 + p[MLP_OFF_W3 + 64 + u] * d1) * (1.0f - h * h);
-            }
-        }
-    __syncthreads();
-
-    float *out = a.partial + (long)blockIdx.x * NP;
-    // dL/dW3[o][u] = sum_s dy_o h2[s][u]; lane = u
-    {
-        float g0 = 0.f, g1 = 0.f;
-        for (int s = 0; s < 64; ++s) {
-            const float h = H2[s * LDS_STRIDE + lane];
-            g0 += DY[s][0] * h;
-            g1 += DY[s][1] * h;
-        }
-        out[P_W3 + lane] = g0;
-        out[P_W3 + 64 + lane] = g1;
-        float b2 = 0.f;
-        for (int s = 0; s < 64; ++s) b2 += DZ2[s * LDS_STRIDE + lane];
-        out[P_B2 + lane] = b2;
-    }
-    if (lane < 6) {
-        const int o = lane / 3, w = lane % 3;
-        float acc1 = 0.f;
-        for (int s = 0; s < 64; ++s) acc1 += DY[s][o] * (w == 0 ? 1.0f : XS[s][w - 1]);
-        if (w == 0) out[P_B3 + o] = acc1;
-        else out[P_WS + o * 2 + (w - 1)] = acc1;
-    }
-
-    // dL/dh1^T = W2^T dz2^T on the matrix cores: A = W2^T, B[k = u][n = s]
-    const bf16x8 *thi = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2THI);
-    const bf16x8 *tlo = reinterpret_cast<const bf16x8 *>(p + MLP_OFF_W2TLO);
-    f32x16 dh[2][2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dh[mt][nt][i] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        bf16x8 bh[2], bl[2];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int ks = 0; ks < 4; ++ks) {
             float v[8];
-            const int s = 32 * nt + l32;
+            bf16x8 bh, bl;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = DZ2[s * LDS_STRIDE + 16 * ks + 8 * g + e];
-            split8(v, bh[nt], bl[nt]);
+            for (int e = 0; e < 8; ++e) v[e] = H1[(32 * nt + l32) * LDS_STRIDE + 16 * ks + 8 * g + e];
+            split8(v, bh, bl);
+            acc = mfma3(w2h[ks], w2l[ks], bh, bl, acc);
         }
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const bf16x8 ah = thi[(mt * 4 + ks) * 64 + lane], al = tlo[(mt * 4 + ks) * 64 + lane];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) dh[mt][nt] = mfma3(ah, al, bh[nt], bl[nt], dh[mt][nt]);
+        for (int i = 0; i < 16; ++i) {
+            const float h = fast_tanh(acc[i] + reinterpret_cast<const float *>(b2)[i]);
+            h2[i] = h;
+            H2[(32 * nt + l32) * LDS_STRIDE + mlp_unit(mt, i, g)] = h;
         }
+    } else if (head) {
+        double tP, tR;
+        table_lookup<double>(a.op, double(lr), double(lt), tP, tR);
+        t0 = float((tP - a.op.norm[0]) / a.op.norm[1]);
+        t1 = float((tR - a.op.norm[2]) / a.op.norm[3]);
     }
-    __syncthreads();   // every lane is done reading H2 (dW3) before dz1 overwrites it
-    float *DZ1 = H2;
+    __syncthreads();
+
+    // output layer: one sample a lane, wavefront = output and half of the units
+    if (tiles) {
+        const int o = w & 1, half = w >> 1;
+        float part = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int s = 32 * nt + l32;
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int k = MlpWave::unit(mt, i, g);
-                const float h = H1[s * LDS_STRIDE + k];
-                DZ1[s * LDS_STRIDE + k] = dh[mt][nt][i] * (1.0f - h * h);
+                const int u = mlp_unit(m, i, half);
+                part += W3[64 * o + u] * H2[lane * LDS_STRIDE + u];
             }
-        }
+        PART[o][half][lane] = part;
+    }
+    __syncthreads();
 
-    // dL/dW2 = dz2^T h1 with K = samples: A[m = u][k = s], B[k = s][n = k_in]
-    f32x16 gw[2][2];
+    float lossl = 0.f;
+    if (head) {
+        const float y0 = PART[0][0][lane] + PART[0][1][lane] + b3[0] + ws[0] * x0 + ws[1] * x1;
+        const float y1 = PART[1][0][lane] + PART[1][1][lane] + b3[1] + ws[2] * x0 + ws[3] * x1;
+        const float e0 = y0 - t0, e1 = y1 - t1;
+        lossl = 0.5f * (e0 * e0 + e1 * e1) * a.inv_batch;
+        DY[lane] = e0 * a.inv_batch;
+        DY[64 + lane] = e1 * a.inv_batch;
+    }
+    __syncthreads();
+
+    // dz2 = (W3^T dy) * (1 - h2^2)
+    if (tiles) {
+        const float d0 = DY[32 * nt + l32], d1 = DY[64 + 32 * nt + l32];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+        for (int i = 0; i < 16; ++i) {
+            const int u = mlp_unit(mt, i, g);
+            DZ2[(32 * nt + l32) * LDS_STRIDE + u] = (W3[u] * d0 + W3[64 + u] * d1) * (1.0f - h2[i] * h2[i]);
+        }
+    }
+    __syncthreads();
+
+    float sum2 = 0.f;
+    if (tiles) {
+        // dL/dh1^T = W2^T dz2^T: A = W2^T, B[k = u][n = s]
+        f32x16 dh;
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int i = 0; i < 16; ++i) dh[i] = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) gw[mt][nt][i] = 0.f;
+        for (int ks = 0; ks < 4; ++ks) {
+            float v[8];
+            bf16x8 bh, bl;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        bf16x8 ah[2], al[2], bh[2], bl[2];
+            for (int e = 0; e < 8; ++e) v[e] = DZ2[(32 * nt + l32) * LDS_STRIDE + 16 * ks + 8 * g + e];
+            split8(v, bh, bl);
+            dh = mfma3(wth[ks], wtl[ks], bh, bl, dh);
+        }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int i = 0; i < 16; ++i) {
+            const int q = (32 * nt + l32) * LDS_STRIDE + mlp_unit(mt, i, g);
+            const float h = H1[q];
+            DZ1[q] = dh[i] * (1.0f - h * h);
+        }
+    } else if (!head) {
+        // lane = unit: dL/dW3[o][u] = sum_s dy_o h2[s][u] (o = 0, 1) and dL/db2[u]
+        sum2 = w < 7 ? dot64(H2 + lane, DY + 64 * (w - 5)) : sum64(DZ2 + lane);
+    } else {
+        // dL/db3 and dL/dWs: lanes 0..5 are (output, input or bias)
+        const int o = lane < 3 ? 0 : 1, q = lane < 6 ? lane - 3 * o : 0;
+        float acc = 0.f;
+#pragma unroll
+        for (int s = 0; s < 64; s += 4) {
+            const float4 d = DYq[16 * o + s / 4], x = X1q[16 * q + s / 4];
+            acc += d.x * x.x;
+            acc += d.y * x.y;
+            acc += d.z * x.z;
+            acc += d.w * x.w;
+        }
+        if (lane < 6) out[q == 2 ? P_B3 + o : P_WS + o * 2 + q] = acc;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) lossl += __shfl_xor(lossl, o);
+        if (lane == 0) a.loss_part[blockIdx.x] = lossl;
+    }
+    __syncthreads();
+
+    if (tiles) {
+        // dL/dW2 = dz2^T h1 with K = samples: A[m = u][k = s], B[k = s][n = k_in]
+        f32x16 gw;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gw[i] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
             float va[8], vb[8];
+            bf16x8 ah, al, bh, bl;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int s = 16 * ks + 8 * g + e;
-                va[e] = DZ2[s * LDS_STRIDE + 32 * t + l32];
-                vb[e] = H1[s * LDS_STRIDE + 32 * t + l32];
+                va[e] = DZ2[s * LDS_STRIDE + 32 * mt + l32];
+                vb[e] = H1[s * LDS_STRIDE + 32 * nt + l32];
             }
-            split8(va, ah[t], al[t]);
-            split8(vb, bh[t], bl[t]);
+            split8(va, ah, al);
+            split8(vb, bh, bl);
+            gw = mfma3(ah, al, bh, bl, gw);
         }
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) gw[mt][nt] = mfma3(ah[mt], al[mt], bh[nt], bl[nt], gw[mt][nt]);
+        for (int i = 0; i < 16; ++i) out[P_W2 + mlp_unit(mt, i, g) * 64 + 32 * nt + l32] = gw[i];
+    } else if (!head) {
+        // lane = unit: dL/dW1 (x0, x1) and dL/db1
+        const float sum1 = w < 7 ? dot64(DZ1 + lane, X1 + 64 * (w - 5)) : sum64(DZ1 + lane);
+        out[w < 7 ? P_W3 + 64 * (w - 5) + lane : P_B2 + lane] = sum2;
+        out[w < 7 ? P_W1 + 2 * lane + (w - 5) : P_B1 + lane] = sum1;
     }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int u = MlpWave::unit(mt, i, g);
-                out[P_W2 + u * 64 + 32 * nt + l32] = gw[mt][nt][i];
-            }
-    __syncthreads();   // dz1 complete
-    {
-        float gw0 = 0.f, gw1 = 0.f, gb = 0.f;
-        for (int s = 0; s < 64; ++s) {
-            const float d = DZ1[s * LDS_STRIDE + lane];
-            gw0 += d * XS[s][0];
-            gw1 += d * XS[s][1];
-            gb += d;
-        }
-        out[P_W1 + 2 * lane] = gw0;
-        out[P_W1 + 2 * lane + 1] = gw1;
-        out[P_B1 + lane] = gb;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lossl += __shfl_xor(lossl, o);
-    if (lane == 0) a.loss_part[blockIdx.x] = lossl;
 }
 
 // ---------------------------------------------------------------------------
@@ -389,45 +440,71 @@ __device__ __forceinline__ unsigned short dev_bf16_bits(float v)
     return __builtin_bit_cast(unsigned short, b);
 }
 
-// Sum of the nblk per-wavefront partial gradients of parameter i, in a
+// Sum of the nblk per-block partial gradients of parameter i, in a
 // fixed order shared by the Adam and gradient kernels (so both produce the
 // same bits): a 256-thread block owns 64 consecutive parameters (one per
 // lane); wavefront w adds the partials of the contiguous quarter
-// [w q, w q + q) of the waves in order, and the first wavefront adds the
+// [w q, w q + q) of the blocks in order, and the first wavefront adds the
 // four quarter sums in order w = 0..3.  Returns the sum in the threads of
 // the first wavefront (i < NP); the other threads return 0.
-constexpr int RED_PARAMS = 64;
+constexpr int RED_PARAMS = 64, RED_BLOCKS = (NP + RED_PARAMS - 1) / RED_PARAMS;
 
 __device__ __forceinline__ float reduce_partials(const float *partial, int nblk, int i, float (&sh)[4][64])
 {
+    constexpr int DEEP = 16;   // loads in flight (one after the other took 8.4 us at 64 blocks, now 3.8)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int q = (nblk + 3) >> 2;
     const int b0 = w * q, b1 = b0 + q < nblk ? b0 + q : nblk;
     float g = 0.f;
-    if (i < NP)
-        for (int b = b0; b < b1; ++b) g += partial[(long)b * NP + i];
+    if (i < NP) {
+        int b = b0;
+        for (; b + DEEP <= b1; b += DEEP) {
+            float v[DEEP];
+#pragma unroll
+            for (int e = 0; e < DEEP; ++e) v[e] = partial[(long)(b + e) * NP + i];
+#pragma unroll
+            for (int e = 0; e < DEEP; ++e) g += v[e];
+        }
+        for (; b < b1; ++b) g += partial[(long)b * NP + i];
+    }
     sh[w][lane] = g;
     __syncthreads();
     if (w != 0) return 0.f;
     return ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
 }
 
+// Sum of the loss parts in their order, by one wavefront: 64 loaded at once,
+// then added one by one.
+__device__ __forceinline__ float sum_loss(const float *part, int nblk)
+{
+    const int lane = threadIdx.x & 63;
+    float L = 0.f;
+    for (int b = 0; b < nblk; b += 64) {
+        const float v = b + lane < nblk ? part[b + lane] : 0.f;
+        const int m = nblk - b < 64 ? nblk - b : 64;
+        for (int l = 0; l < m; ++l) L += lane_value(v, l);
+    }
+    return L;
+}
+
 __global__ void __launch_bounds__(256) k_mlp_adam(AdamArgs a)
 {
     __shared__ float sh[4][64];
     const int i = blockIdx.x * RED_PARAMS + (threadIdx.x & 63);
-    if (blockIdx.x == 0 && threadIdx.x == 64) {
-        float L = 0.f;
-        for (int b = 0; b < a.nblk; ++b) L += a.loss_part[b];
-        a.loss_hist[a.step] = L;
+    if (blockIdx.x == RED_BLOCKS) {   // one more block for the loss
+        const float L = sum_loss(a.loss_part, a.nblk);
+        if (threadIdx.x == 0) a.loss_hist[a.step] = L;
+        return;
     }
+    const int ic = i < NP ? i : NP - 1;
+    const float m0 = a.m[ic], v0 = a.v[ic], th0 = a.theta[ic];
     const float g = reduce_partials(a.partial, a.nblk, i, sh);
     if (threadIdx.x >= 64 || i >= NP) return;
-    const float m = a.b1 * a.m[i] + (1.f - a.b1) * g;
-    const float v = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
+    const float m = a.b1 * m0 + (1.f - a.b1) * g;
+    const float v = a.b2 * v0 + (1.f - a.b2) * g * g;
     a.m[i] = m;
     a.v[i] = v;
-    const float w = a.theta[i] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+    const float w = th0 - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
     a.theta[i] = w;
     // refresh the packed network used by the next forward pass
     float *pk = a.pk;
@@ -457,10 +534,10 @@ __global__ void __launch_bounds__(256) k_mlp_reduce(const float *partial, int nb
 {
     __shared__ float sh[4][64];
     const int i = blockIdx.x * RED_PARAMS + (threadIdx.x & 63);
-    if (blockIdx.x == 0 && threadIdx.x == 64) {
-        float L = 0.f;
-        for (int b = 0; b < nblk; ++b) L += loss_part[b];
-        *loss = L;
+    if (blockIdx.x == RED_BLOCKS) {
+        const float L = sum_loss(loss_part, nblk);
+        if (threadIdx.x == 0) *loss = L;
+        return;
     }
     const float g = reduce_partials(partial, nblk, i, sh);
     if (threadIdx.x < 64 && i < NP) grad[i] = g;
@@ -619,13 +696,13 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
     aa.loss_hist = loss_hist;
     for (long s = 0; s < cfg->steps && e == hipSuccess; ++s) {
         ta.offset = (s * (long)cfg->batch) % cfg->n_train;
-        hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(nblk), dim3(64), 0, c->stream, ta);
+        hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(nblk), dim3(TRAIN_THREADS), 0, c->stream, ta);
         const double frac = cfg->steps > 1 ? double(s) / double(cfg->steps - 1) : 1.0;
         aa.lr = float(cfg->lr_final + 0.5 * (cfg->lr - cfg->lr_final) * (1.0 + std::cos(M_PI * frac)));
         aa.c1 = float(1.0 - std::pow(cfg->beta1, double(s + 1)));
         aa.c2 = float(1.0 - std::pow(cfg->beta2, double(s + 1)));
         aa.step = s;
-        hipLaunchKernelGGL(k_mlp_adam, dim3((NP + RED_PARAMS - 1) / RED_PARAMS), dim3(256), 0, c->stream, aa);
+        hipLaunchKernelGGL(k_mlp_adam, dim3(RED_BLOCKS + 1), dim3(256), 0, c->stream, aa);
         e = hipGetLastError();
     }
     hipEventRecord(ev1, c->stream);
@@ -689,8 +766,8 @@ int mlp_gradient(m1_ctx *c, const float *samples, long n, const float *theta, fl
     ta.op = c->op;
     ta.partial = partial;
     ta.loss_part = loss_part;
-    hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(nblk), dim3(64), 0, c->stream, ta);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NP + RED_PARAMS - 1) / RED_PARAMS), dim3(256), 0, c->stream, partial, nblk,
+    hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(nblk), dim3(TRAIN_THREADS), 0, c->stream, ta);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3(RED_BLOCKS + 1), dim3(256), 0, c->stream, partial, nblk,
                        loss_part, g, L);
     float Lh = 0.f;
     hipError_t e = hipGetLastError();

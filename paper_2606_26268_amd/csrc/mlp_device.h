@@ -1,17 +1,14 @@
 // mlp_device.h -- wavefront-cooperative evaluation of the opacity surrogate
 //   x (2) -> h1 = tanh(W1 x + b1) (64) -> h2 = tanh(W2 h1 + b2) (64)
 //         -> y = W3 h2 + b3 + Ws x (2),  log10 kappa = y * std + mean
-// for 64 inputs at once (one per lane).  The training form (MlpWave) runs layers
-// 1 and 3 on the vector ALU in FP32 and the 64x64 layer on the bfloat16 matrix
-// cores (v_mfma_f32_32x32x16_bf16, FP32 accumulation) with each operand split
-// into a bfloat16 high part and a bfloat16 remainder, keeping hi*hi + hi*lo +
-// lo*hi (about 16 significant bits per product); the inference form further
-// down splits the 64x64 layer in half precision.
+// for 64 inputs at once (one per lane), both hidden layers on the matrix cores
+// with split operands (see the inference section below; training has its own
+// form in mlp.hip).
 //
 // Matrix-core operand layout used (32x32x16): lane l, g = l / 32, holds
 //   A[m = l % 32][k = 8 g + e], B[k = 8 g + e][n = l % 32], e = 0..7,
 //   D[row = 8 (i / 4) + 4 g + (i % 4)][col = l % 32], i = 0..15.
-// The product is computed as Z2^T = W2 * H1^T: A = W2 (rows: output units),
+// The 64x64 product is computed as Z2^T = W2 * H1^T: A = W2 (rows: output units),
 // B = H1^T (columns: samples).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -83,137 +80,27 @@ __device__ __forceinline__ float net_kappa(float y, float sd, float mean)
     return __builtin_amdgcn_exp2f((y * sd + mean) * 3.3219280948873623f);
 }
 
-struct MlpWave {
-    const float *p;
-    bf16x8 w2h[2][4], w2l[2][4];
+// Unit (row) held in slot i of 32-row tile mt by lane group g of a matrix-core
+// product.
+__host__ __device__ __forceinline__ constexpr int mlp_unit(int mt, int i, int g)
+{
+    return 32 * mt + 8 * (i >> 2) + 4 * g + (i & 3);
+}
 
-    __device__ __forceinline__ void load(const float *packed, int lane)
-    {
-        p = packed;
-        const bf16x8 *hi = reinterpret_cast<const bf16x8 *>(packed + MLP_OFF_W2HI);
-        const bf16x8 *lo = reinterpret_cast<const bf16x8 *>(packed + MLP_OFF_W2LO);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                w2h[mt][ks] = hi[(mt * 4 + ks) * 64 + lane];
-                w2l[mt][ks] = lo[(mt * 4 + ks) * 64 + lane];
-            }
-    }
-
-    // Layer 1 for the lane's own input: h1[0..63].
-    __device__ __forceinline__ void layer1(float x0, float x1, float h1[64]) const
-    {
-#pragma unroll
-        for (int u = 0; u < 64; ++u)
-            h1[u] = fast_tanh(p[MLP_OFF_W1 + 2 * u] * x0 + p[MLP_OFF_W1 + 2 * u + 1] * x1 +
-                              p[MLP_OFF_B1 + u]);
-    }
-
-    // Layer 2 pre-activations Z2^T tiles acc[mt][nt]: lane holds samples
-    // 32 nt + l % 32, output units 32 mt + 8 (i / 4) + 4 g + (i % 4).
-    __device__ __forceinline__ void layer2(const float h1[64], int lane, f32x16 acc[2][2]) const
-    {
-        const int g = lane >> 5;
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.0f;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            // own values of chunk g and the partner's (lane ^ 32) of chunk g
-            bf16x8 own_h, own_l, oth_h, oth_l;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float mine = g ? h1[16 * ks + 8 + e] : h1[16 * ks + e];
-                const float send = g ? h1[16 * ks + e] : h1[16 * ks + 8 + e];
-                const float recv = __shfl_xor(send, 32);
-                const __bf16 mh = to_bf16(mine), rh = to_bf16(recv);
-                own_h[e] = mh;
-                own_l[e] = to_bf16(mine - float(mh));
-                oth_h[e] = rh;
-                oth_l[e] = to_bf16(recv - float(rh));
-            }
-            // tile nt: lanes of group nt supply their own sample
-            const bf16x8 b0h = g == 0 ? own_h : oth_h, b0l = g == 0 ? own_l : oth_l;
-            const bf16x8 b1h = g == 1 ? own_h : oth_h, b1l = g == 1 ? own_l : oth_l;
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                acc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2h[mt][ks], b0h, acc[mt][0], 0, 0, 0);
-                acc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2h[mt][ks], b0l, acc[mt][0], 0, 0, 0);
-                acc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2l[mt][ks], b0h, acc[mt][0], 0, 0, 0);
-                acc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2h[mt][ks], b1h, acc[mt][1], 0, 0, 0);
-                acc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2h[mt][ks], b1l, acc[mt][1], 0, 0, 0);
-                acc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2l[mt][ks], b1h, acc[mt][1], 0, 0, 0);
-            }
-        }
-    }
-
-    // Output unit held in slot i of tile mt by lane group g.
-    static __device__ __forceinline__ int unit(int mt, int i, int g)
-    {
-        return 32 * mt + 8 * (i >> 2) + 4 * g + (i & 3);
-    }
-
-    // Full forward for the lane's own input x -> y (normalised outputs).
-    __device__ __forceinline__ void forward(float x0, float x1, int lane, float &y0, float &y1) const
-    {
-        float h1[64];
-        layer1(x0, x1, h1);
-        f32x16 acc[2][2];
-        layer2(h1, lane, acc);
-        const int g = lane >> 5;
-        float part[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // [nt][output]
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int u = unit(mt, i, g);
-                    const float h2 = fast_tanh(acc[mt][nt][i] + p[MLP_OFF_B2 + u]);
-                    part[nt][0] += p[MLP_OFF_W3 + u] * h2;
-                    part[nt][1] += p[MLP_OFF_W3 + 64 + u] * h2;
-                }
-        // the partner lane holds the other 32 units of the same samples
-        const float s0 = g ? part[0][0] : part[1][0];
-        const float s1 = g ? part[0][1] : part[1][1];
-        const float r0 = __shfl_xor(s0, 32), r1 = __shfl_xor(s1, 32);
-        const float m0 = g ? part[1][0] : part[0][0];
-        const float m1 = g ? part[1][1] : part[0][1];
-        y0 = m0 + r0 + p[MLP_OFF_B3] + p[MLP_OFF_WS] * x0 + p[MLP_OFF_WS + 1] * x1;
-        y1 = m1 + r1 + p[MLP_OFF_B3 + 1] + p[MLP_OFF_WS + 2] * x0 + p[MLP_OFF_WS + 3] * x1;
-    }
-
-    // Network inputs from (rho, T) through the table axes and offsets.
-    static __device__ __forceinline__ void inputs(const OpacityParams &op, float rho, float T, float &x0,
-                                                  float &x1)
-    {
-        // log10 through the hardware log2 (the network inputs carry FP32
-        // rounding in any case), clamped to the table axes
-        constexpr float LOG10_2 = 0.30102999566398120f;
-        const auto &q = op.f32;
-        float lr = __builtin_amdgcn_logf(rho) * LOG10_2 + q.lr_off;
-        float lt = __builtin_amdgcn_logf(T) * LOG10_2 + q.lt_off;
-        lr = __builtin_fminf(__builtin_fmaxf(lr, q.lr0), q.lr1);
-        lt = __builtin_fminf(__builtin_fmaxf(lt, q.lt0), q.lt1);
-        x0 = 2.0f * (lr - q.lr0) * q.lr_inv - 1.0f;
-        x1 = 2.0f * (lt - q.lt0) * q.lt_inv - 1.0f;
-    }
-
-    __device__ __forceinline__ void opacity(const OpacityParams &op, float rho, float T, int lane, float &kP,
-                                            float &kR) const
-    {
-        float x0, x1, y0, y1;
-        inputs(op, rho, T, x0, x1);
-        forward(x0, x1, lane, y0, y1);
-        kP = net_kappa(y0, p[MLP_OFF_NORM + 1], p[MLP_OFF_NORM + 0]);
-        kR = net_kappa(y1, p[MLP_OFF_NORM + 3], p[MLP_OFF_NORM + 2]);
-    }
-};
-
+// Network inputs from (rho, T) through the table axes and offsets.
+__device__ __forceinline__ void mlp_inputs(const OpacityParams &op, float rho, float T, float &x0, float &x1)
+{
+    // log10 through the hardware log2 (the network inputs carry FP32
+    // rounding in any case), clamped to the table axes
+    constexpr float LOG10_2 = 0.30102999566398120f;
+    const auto &q = op.f32;
+    float lr = __builtin_amdgcn_logf(rho) * LOG10_2 + q.lr_off;
+    float lt = __builtin_amdgcn_logf(T) * LOG10_2 + q.lt_off;
+    lr = __builtin_fminf(__builtin_fmaxf(lr, q.lr0), q.lr1);
+    lt = __builtin_fminf(__builtin_fmaxf(lt, q.lt0), q.lt1);
+    x0 = 2.0f * (lr - q.lr0) * q.lr_inv - 1.0f;
+    x1 = 2.0f * (lt - q.lt0) * q.lt_inv - 1.0f;
+}
 
 // ---------------------------------------------------------------------------
 // Inference form.  A wavefront evaluates 64 inputs as two 32-sample column
@@ -348,7 +235,7 @@ __device__ __forceinline__ void mlp_image_entry(const float *W1, const float *b1
         // the output layer takes h2 = 1 - 2 r (r = 1 / (1 + 2^z)) as
         // sum W3 - 2 sum W3 r: weights -2 W3 per unit, the sum once per output
         const int q = t - 256, g = q >> 5, mt = (q >> 4) & 1, i = q & 15;
-        const int u = MlpWave::unit(mt, i, g);
+        const int u = mlp_unit(mt, i, g);
         img.ep[g][mt][i] = make_float2(-2.0f * W3[u], -2.0f * W3[64 + u]);
     } else if (t < 384) {
         const int lane = t - 320;
@@ -472,7 +359,7 @@ __device__ __forceinline__ void mlp_opacity_shared(const OpacityParams &op, cons
 {
     const float *p = op.mlp;
     float x0, x1, y0, y1;
-    MlpWave::inputs(op, rho, T, x0, x1);
+    mlp_inputs(op, rho, T, x0, x1);
     mlp_forward_shared(p, sh, x0, x1, lane, y0, y1);
     kP = net_kappa(y0, p[MLP_OFF_NORM + 1], p[MLP_OFF_NORM + 0]);
     kR = net_kappa(y1, p[MLP_OFF_NORM + 3], p[MLP_OFF_NORM + 2]);

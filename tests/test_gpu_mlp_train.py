@@ -1,0 +1,48 @@
+"""Batch gradient of the opacity network at block counts that end inside,
+at and past the reduction's load depth and quarters, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_26268_amd import inputs as I
+from tests.gpu_common import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("blocks", [1, 5, 61, 64, 67, 141])
+def test_gradient_over_block_counts(orc, blocks):
+    """64 samples a block.  Each layer's gradient within 1e-4 relative L2 of
+    the FP64 gradient with the same bfloat16 splits: the split leaves 2^-16 of a
+    product, FP32 sums 2^-24 per term, so 1e-5 is expected and a wrong, missing or
+    doubled block (1 / blocks of the sum) is far outside."""
+    from paper_2606_26268_amd import m1
+    tab = I.make_table()
+    p = I.make_uniform(I.CARTESIAN, (64, 1, 1), 1)
+    p.opacity = tab
+    rng = np.random.default_rng(blocks)
+    th = (I.mlp_init(7).astype(np.float64) + 0.05 * rng.normal(size=m1.M1_MLP_NPARAM)).astype(np.float32)
+    norm = np.array([f(tab[k].astype(np.float64)) for k in ("log10_kP", "log10_kR") for f in (np.mean, np.std)])
+    s = m1.Solver(p, "p64")
+    m1.m1_set_opacity_mlp(s.ctx, th, norm)
+    n = 64 * blocks
+    smp = I.mlp_samples(n, 1000 + blocks)
+    loss, g = m1.m1_mlp_gradient(s.ctx, torch.from_numpy(smp).to("cuda"), n, th)
+    s.close()
+    q = I.make_uniform(I.CARTESIAN, (2, 1, 1), 1)
+    q.opacity = tab
+    lr, lt = smp[:, 0].astype(np.float64), smp[:, 1].astype(np.float64)
+    kP, kR = orc.Oracle(q).opacity(10 ** (lr - tab["lr_off"]), 10 ** (lt - tab["lt_off"]))
+    t = np.stack([(np.log10(kP) - norm[0]) / norm[1], (np.log10(kR) - norm[2]) / norm[3]], axis=1)
+    x = np.stack([2 * (lr - tab["lr0"]) / (tab["lr1"] - tab["lr0"]) - 1,
+                  2 * (lt - tab["lt0"]) / (tab["lt1"] - tab["lt0"]) - 1], axis=1)
+    rloss, rg = orc.mlp_loss_grad(th.astype(np.float64), x, t, bf16=True)
+    assert abs(loss - rloss) <= 1e-4 * rloss
+    off, worst = 0, 0.0
+    for name, shp in I.MLP_LAYOUT:
+        k = int(np.prod(shp))
+        err = np.linalg.norm(g[off:off + k] - rg[off:off + k]) / np.linalg.norm(rg[off:off + k])
+        worst = max(worst, float(err))
+        assert err <= 1e-4, (name, err)
+        off += k
+    say(f"  gradient over {blocks} blocks: largest rel-L2 of a layer {worst:.2e}")
