@@ -539,6 +539,7 @@ m1_status m1_set_opacity_table(m1_ctx *c, int nr, int nt, double lr0, double lr1
     }
     if (c->table_dev) hipFree(c->table_dev);
     c->table_dev = tab;
+    mlp_table_stats(kP, kR, nr, nt, c->tab_norm, c->tab_lin);
     c->op.kind = OPK_TABLE;
     c->op.nr = nr;
     c->op.nt = nt;

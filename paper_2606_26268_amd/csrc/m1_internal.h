@@ -173,6 +173,8 @@ struct m1_ctx {
     // opacity
     m1::OpacityParams op{};
     float *table_dev = nullptr;            // [2][nt][nr], then the cell records
+    double tab_norm[4] = {};               // mean and std of the bound table's log10 kappa_P, kappa_R
+    float tab_lin[2][3] = {};              // and their least-squares planes (mlp_table_stats)
     float *mlp_dev = nullptr;              // packed network
     std::vector<float> mlp_theta;          // host copy of the float32 master
 };
@@ -203,6 +205,7 @@ hipError_t launch_implicit_rk2(m1_ctx *c, double dt, int stage);
 bool fused_stages(const m1_ctx *c);        // whether the two below serve the context
 hipError_t launch_stage(m1_ctx *c, double dt, int stage);
 hipError_t launch_transport_from(m1_ctx *c, double dt, const void *const rad[4]);
+void mlp_table_stats(const float *kP, const float *kR, int nr, int nt, double norm[4], float lin[2][3]);
 int mlp_pack(m1_ctx *c, const float *theta, const double *norm);
 int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep);
 int mlp_gradient(m1_ctx *c, const float *samples, long n, const float *theta, float *grad, double *loss);

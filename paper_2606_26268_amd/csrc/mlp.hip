@@ -43,23 +43,6 @@ __host__ __device__ __forceinline__ int frag_slot(int m, int k)
     return ((mt * 4 + ks) * 64 + lane) * 8 + e;
 }
 
-static inline unsigned short host_bf16_bits(float v)
-{
-    unsigned int u;
-    std::memcpy(&u, &v, 4);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (unsigned short)(u >> 16);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-
-static inline float host_bf16_value(unsigned short b)
-{
-    unsigned int u = (unsigned int)b << 16;
-    float f;
-    std::memcpy(&f, &u, 4);
-    return f;
-}
-
 // The inference form's LDS image in the packed network, from the flat
 // parameters: the split fragments of A2 = -2 s 2^-e W2, one W2 element per
 // thread, and the layer-1, layer-2 start and output entries (mlp_image_entry).
@@ -90,55 +73,84 @@ __global__ void __launch_bounds__(256) k_mlp_pack_infer(const float *theta, floa
     mlp_image_entry(theta + P_W1, theta + P_B1, theta + P_W2, theta + P_B2, theta + P_W3, se, img, t);
 }
 
-static void host_pack(const float *th, const double *norm, std::vector<float> &pk)
+// One parameter's entries in the packed network (all but the inference image).
+__device__ __forceinline__ void pack_param(float *pk, int i, float w)
 {
-    pk.assign(MLP_TRAIN_PACK, 0.0f);
-    for (int i = 0; i < NP; ++i) pk[MLP_OFF_THETA + i] = th[i];
-    for (int i = 0; i < 128; ++i) pk[MLP_OFF_W1 + i] = th[P_W1 + i];
-    for (int i = 0; i < 64; ++i) pk[MLP_OFF_B1 + i] = th[P_B1 + i];
-    for (int i = 0; i < 64; ++i) pk[MLP_OFF_B2 + i] = th[P_B2 + i];
-    for (int i = 0; i < 128; ++i) pk[MLP_OFF_W3 + i] = th[P_W3 + i];
-    for (int i = 0; i < 2; ++i) pk[MLP_OFF_B3 + i] = th[P_B3 + i];
-    for (int i = 0; i < 4; ++i) pk[MLP_OFF_WS + i] = th[P_WS + i];
-    for (int i = 0; i < 4; ++i) pk[MLP_OFF_NORM + i] = float(norm[i]);
-    unsigned short *hi = reinterpret_cast<unsigned short *>(&pk[MLP_OFF_W2HI]);
-    unsigned short *lo = reinterpret_cast<unsigned short *>(&pk[MLP_OFF_W2LO]);
-    unsigned short *thi = reinterpret_cast<unsigned short *>(&pk[MLP_OFF_W2THI]);
-    unsigned short *tlo = reinterpret_cast<unsigned short *>(&pk[MLP_OFF_W2TLO]);
-    for (int u = 0; u < 64; ++u)
-        for (int k = 0; k < 64; ++k) {
-            const float w = th[P_W2 + u * 64 + k];
-            const unsigned short h = host_bf16_bits(w);
-            const unsigned short l = host_bf16_bits(w - host_bf16_value(h));
-            hi[frag_slot(u, k)] = h;
-            lo[frag_slot(u, k)] = l;
-            thi[frag_slot(k, u)] = h;
-            tlo[frag_slot(k, u)] = l;
-        }
+    if (i < P_B1) pk[MLP_OFF_W1 + i] = w;
+    else if (i < P_W2) pk[MLP_OFF_B1 + (i - P_B1)] = w;
+    else if (i < P_B2) {
+        const int u = (i - P_W2) >> 6, k = (i - P_W2) & 63;
+        const __bf16 h = to_bf16(w), l = to_bf16(w - float(h));
+        reinterpret_cast<__bf16 *>(pk + MLP_OFF_W2HI)[frag_slot(u, k)] = h;
+        reinterpret_cast<__bf16 *>(pk + MLP_OFF_W2LO)[frag_slot(u, k)] = l;
+        reinterpret_cast<__bf16 *>(pk + MLP_OFF_W2THI)[frag_slot(k, u)] = h;
+        reinterpret_cast<__bf16 *>(pk + MLP_OFF_W2TLO)[frag_slot(k, u)] = l;
+    } else if (i < P_W3) pk[MLP_OFF_B2 + (i - P_B2)] = w;
+    else if (i < P_B3) pk[MLP_OFF_W3 + (i - P_W3)] = w;
+    else if (i < P_WS) pk[MLP_OFF_B3 + (i - P_B3)] = w;
+    else pk[MLP_OFF_WS + (i - P_WS)] = w;
+}
+
+// The entries other than the inference image from the flat parameters at
+// MLP_OFF_THETA, and the normalisation.  With `adam` ([3][NP]) also the start of
+// a training run: two moments of zero and the parameters.
+constexpr int PACK_BLOCKS = (NP + 255) / 256;
+
+__global__ void __launch_bounds__(256) k_mlp_pack(float *pk, float4 norm, float *adam)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < 4) pk[MLP_OFF_NORM + i] = i == 0 ? norm.x : i == 1 ? norm.y : i == 2 ? norm.z : norm.w;
+    if (i >= NP) return;
+    const float w = pk[MLP_OFF_THETA + i];
+    pack_param(pk, i, w);
+    if (adam) {
+        adam[i] = 0.f;
+        adam[NP + i] = 0.f;
+        adam[2 * NP + i] = w;
+    }
+}
+
+// Parameters and normalisation to the device and k_mlp_pack, in the context's
+// stream; theta must stay as it is until the stream is synchronised.  What the
+// caller queued on the default stream (the samples, say) is waited for, also
+// where the context's stream does not wait for that one by itself.
+static hipError_t upload_network(m1_ctx *c, const float *theta, const double *norm, float *adam)
+{
+    hipError_t e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return e;
+    e = hipMemcpyAsync(c->mlp_dev + MLP_OFF_THETA, theta, NP * sizeof(float), hipMemcpyHostToDevice, c->stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mlp_pack, dim3(PACK_BLOCKS), dim3(256), 0, c->stream, c->mlp_dev,
+                       make_float4(float(norm[0]), float(norm[1]), float(norm[2]), float(norm[3])), adam);
+    return hipGetLastError();
+}
+
+static hipError_t mlp_buffer(m1_ctx *c)
+{
+    if (c->mlp_dev) return hipSuccess;
+    return device_alloc(reinterpret_cast<void **>(&c->mlp_dev), MLP_TRAIN_PACK * sizeof(float));
 }
 
 int mlp_pack(m1_ctx *c, const float *theta, const double *norm)
 {
-    std::vector<float> pk;
-    host_pack(theta, norm, pk);
-    if (!c->mlp_dev) {
-        if (device_alloc(reinterpret_cast<void **>(&c->mlp_dev), MLP_TRAIN_PACK * sizeof(float)) != hipSuccess) {
-            set_error("MLP buffer allocation failed");
-            return -2;
-        }
+    if (mlp_buffer(c) != hipSuccess) {
+        set_error("MLP buffer allocation failed");
+        return -2;
     }
-    hipError_t e = hipMemcpy(c->mlp_dev, pk.data(), MLP_TRAIN_PACK * sizeof(float), hipMemcpyHostToDevice);
+    std::vector<float> host(theta, theta + NP);
+    hipError_t e = upload_network(c, host.data(), norm, nullptr);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_mlp_pack_infer, dim3(16), dim3(256), 0, c->stream, c->mlp_dev + MLP_OFF_THETA,
                            c->mlp_dev);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = es;
     if (e != hipSuccess) {
         set_error(std::string("MLP upload: ") + hipGetErrorString(e));
         return -3;
     }
-    c->mlp_theta.assign(theta, theta + NP);
+    c->mlp_theta.swap(host);
     for (int i = 0; i < 4; ++i) c->op.norm[i] = norm[i];
     c->op.mlp = c->mlp_dev;
     return 0;
@@ -434,12 +446,6 @@ struct AdamArgs {
     long step;
 };
 
-__device__ __forceinline__ unsigned short dev_bf16_bits(float v)
-{
-    const __bf16 b = to_bf16(v);
-    return __builtin_bit_cast(unsigned short, b);
-}
-
 // Sum of the nblk per-block partial gradients of parameter i, in a
 // fixed order shared by the Adam and gradient kernels (so both produce the
 // same bits): a 256-thread block owns 64 consecutive parameters (one per
@@ -507,26 +513,7 @@ __global__ void __launch_bounds__(256) k_mlp_adam(AdamArgs a)
     const float w = th0 - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
     a.theta[i] = w;
     // refresh the packed network used by the next forward pass
-    float *pk = a.pk;
-    if (i < P_B1) pk[MLP_OFF_W1 + i] = w;
-    else if (i < P_W2) pk[MLP_OFF_B1 + (i - P_B1)] = w;
-    else if (i < P_B2) {
-        const int u = (i - P_W2) >> 6, k = (i - P_W2) & 63;
-        const __bf16 h = to_bf16(w);
-        const unsigned short hb = __builtin_bit_cast(unsigned short, h);
-        const unsigned short lb = dev_bf16_bits(w - float(h));
-        unsigned short *hi = reinterpret_cast<unsigned short *>(pk + MLP_OFF_W2HI);
-        unsigned short *lo = reinterpret_cast<unsigned short *>(pk + MLP_OFF_W2LO);
-        unsigned short *thi = reinterpret_cast<unsigned short *>(pk + MLP_OFF_W2THI);
-        unsigned short *tlo = reinterpret_cast<unsigned short *>(pk + MLP_OFF_W2TLO);
-        hi[frag_slot(u, k)] = hb;
-        lo[frag_slot(u, k)] = lb;
-        thi[frag_slot(k, u)] = hb;
-        tlo[frag_slot(k, u)] = lb;
-    } else if (i < P_W3) pk[MLP_OFF_B2 + (i - P_B2)] = w;
-    else if (i < P_B3) pk[MLP_OFF_W3 + (i - P_W3)] = w;
-    else if (i < P_WS) pk[MLP_OFF_B3 + (i - P_B3)] = w;
-    else pk[MLP_OFF_WS + (i - P_WS)] = w;
+    pack_param(a.pk, i, w);
 }
 
 __global__ void __launch_bounds__(256) k_mlp_reduce(const float *partial, int nblk, const float *loss_part,
@@ -591,30 +578,57 @@ __global__ void __launch_bounds__(256) k_mlp_eval(const float *pk, const float *
 // host driver
 // ---------------------------------------------------------------------------
 
-// mean / std of each table and the least-squares plane t = b + w0 x0 + w1 x1
-// (normalised units) used to initialise the linear shortcut
-static void table_stats(const m1_ctx *c, const std::vector<float> &tab, double norm[4], float lin[2][3])
+// Sums of four interleaved parts (a single chain of additions takes four times
+// as long).
+template <typename F>
+static inline double sum4(long n, F f)
 {
-    const int nr = c->op.nr, nt = c->op.nt;
+    double s[4] = {0, 0, 0, 0};
+    long q = 0;
+    for (; q + 4 <= n; q += 4)
+        for (int e = 0; e < 4; ++e) s[e] += f(q + e);
+    for (; q < n; ++q) s[0] += f(q);
+    return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// mean / std of each table and the least-squares plane t = b + w0 x0 + w1 x1
+// (normalised units) used to initialise the linear shortcut.  Taken when a
+// table is bound, where its values are at hand: a training run took 76 us to
+// read a 128 x 128 table back and 81 us for these sums.
+void mlp_table_stats(const float *kP, const float *kR, int nr, int nt, double norm[4], float lin[2][3])
+{
     const long n = (long)nr * nt;
     for (int o = 0; o < 2; ++o) {
-        const float *T = tab.data() + o * n;
-        double s = 0, s2 = 0;
-        for (long q = 0; q < n; ++q) { s += T[q]; s2 += double(T[q]) * T[q]; }
+        const float *T = o ? kR : kP;
+        const double s = sum4(n, [&](long q) { return double(T[q]); });
+        const double s2 = sum4(n, [&](long q) { return double(T[q]) * T[q]; });
         const double mean = s / n, var = s2 / n - mean * mean;
+        const double sd = var > 0 ? std::sqrt(var) : 1.0, inv = 1.0 / sd;
         norm[2 * o] = mean;
-        norm[2 * o + 1] = var > 0 ? std::sqrt(var) : 1.0;
-        // normal equations of the plane fit on the node grid
+        norm[2 * o + 1] = sd;
+        // normal equations of the plane fit on the node grid, row by row
+        const double di = 2.0 / (nr - 1), dj = 2.0 / (nt - 1);
+        const double f1 = sum4(nr, [&](long i) { return di * i - 1.0; });
+        const double f2 = sum4(nr, [&](long i) { return (di * i - 1.0) * (di * i - 1.0); });
         double A[3][3] = {{0}}, b[3] = {0};
-        for (int j = 0; j < nt; ++j)
-            for (int i = 0; i < nr; ++i) {
-                const double f[3] = {1.0, 2.0 * i / (nr - 1) - 1.0, 2.0 * j / (nt - 1) - 1.0};
-                const double t = (T[(long)j * nr + i] - norm[2 * o]) / norm[2 * o + 1];
-                for (int r = 0; r < 3; ++r) {
-                    b[r] += f[r] * t;
-                    for (int q = 0; q < 3; ++q) A[r][q] += f[r] * f[q];
-                }
-            }
+        for (int j = 0; j < nt; ++j) {
+            const float *row = T + (long)j * nr;
+            const double g = dj * j - 1.0;
+            const double t0 = sum4(nr, [&](long i) { return (row[i] - mean) * inv; });
+            const double t1 = sum4(nr, [&](long i) { return (row[i] - mean) * inv * (di * i - 1.0); });
+            b[0] += t0;
+            b[1] += t1;
+            b[2] += g * t0;
+            A[0][0] += nr;
+            A[0][1] += f1;
+            A[0][2] += g * nr;
+            A[1][1] += f2;
+            A[1][2] += g * f1;
+            A[2][2] += g * g * nr;
+        }
+        A[1][0] = A[0][1];
+        A[2][0] = A[0][2];
+        A[2][1] = A[1][2];
         for (int piv = 0; piv < 3; ++piv)          // Gaussian elimination (SPD, no pivoting)
             for (int r = piv + 1; r < 3; ++r) {
                 const double m = A[r][piv] / A[piv][piv];
@@ -635,41 +649,37 @@ static void table_stats(const m1_ctx *c, const std::vector<float> &tab, double n
 
 int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
 {
-    const long n = (long)c->op.nr * c->op.nt;
-    std::vector<float> tab(2 * n);
-    if (hipMemcpy(tab.data(), c->table_dev, 2 * n * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess) {
-        set_error("m1_mlp_train: table download failed");
-        return int(M1_EDEVICE);
-    }
-    double norm[4];
-    float lin[2][3];
-    table_stats(c, tab, norm, lin);
     std::vector<float> th(cfg->theta_init, cfg->theta_init + NP);
     if (!cfg->keep_init)
         for (int o = 0; o < 2; ++o) {
-            th[P_B3 + o] = lin[o][0];
-            th[P_WS + 2 * o] = lin[o][1];
-            th[P_WS + 2 * o + 1] = lin[o][2];
+            th[P_B3 + o] = c->tab_lin[o][0];
+            th[P_WS + 2 * o] = c->tab_lin[o][1];
+            th[P_WS + 2 * o + 1] = c->tab_lin[o][2];
         }
-    int rc = mlp_pack(c, th.data(), norm);
-    if (rc) return int(M1_EDEVICE);
-
     const int nblk = cfg->batch / 64;
     const long n_eval_blocks = (cfg->n_eval + 255) / 256;
-    // host buffers first: a failed host allocation then leaves no device
-    // buffer behind
-    std::vector<float> hist(cfg->steps), em(2 * n_eval_blocks);
+    // what comes back, in one copy: the trained parameters, the loss of each
+    // step, the held-out maxima.  The host buffer first: a failed host
+    // allocation then leaves no device buffer behind
+    const size_t nres = size_t(NP) + cfg->steps + 2 * n_eval_blocks;
+    std::vector<float> res(nres);
     float *buf = nullptr;
-    const size_t nbuf = 3 * size_t(NP) + size_t(nblk) * NP + nblk + cfg->steps + 2 * n_eval_blocks;
+    const size_t nbuf = 2 * size_t(NP) + nres + size_t(nblk) * NP + nblk;
+    if (mlp_buffer(c) != hipSuccess) {
+        set_error("MLP buffer allocation failed");
+        return int(M1_EDEVICE);
+    }
     if (device_alloc(reinterpret_cast<void **>(&buf), nbuf * sizeof(float)) != hipSuccess) {
         set_error("m1_mlp_train: allocation failed");
         return int(M1_ENOMEM);
     }
-    float *theta = buf, *mom = buf + NP, *vel = buf + 2 * NP, *partial = buf + 3 * NP;
-    float *loss_part = partial + size_t(nblk) * NP, *loss_hist = loss_part + nblk;
-    float *evmax = loss_hist + cfg->steps;
-    hipError_t e = hipMemcpyAsync(theta, th.data(), NP * sizeof(float), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(mom, 0, 2 * NP * sizeof(float), c->stream);
+    float *mom = buf, *vel = buf + NP, *theta = buf + 2 * NP;   // as k_mlp_pack sets them
+    float *loss_hist = theta + NP, *evmax = loss_hist + cfg->steps;
+    float *partial = theta + nres, *loss_part = partial + size_t(nblk) * NP;
+    OpacityParams op = c->op;
+    for (int i = 0; i < 4; ++i) op.norm[i] = c->tab_norm[i];
+    op.mlp = c->mlp_dev;
+    hipError_t e = upload_network(c, th.data(), op.norm, buf);
     hipEvent_t ev0, ev1;
     hipEventCreate(&ev0);
     hipEventCreate(&ev1);
@@ -679,7 +689,7 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
     ta.samples = cfg->samples;
     ta.n_train = cfg->n_train;
     ta.inv_batch = 1.0f / float(cfg->batch);
-    ta.op = c->op;
+    ta.op = op;
     ta.partial = partial;
     ta.loss_part = loss_part;
     AdamArgs aa;
@@ -713,15 +723,13 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_mlp_eval, dim3((unsigned)n_eval_blocks), dim3(256), 0, c->stream, c->mlp_dev,
-                           cfg->samples + 2 * cfg->n_train, cfg->n_eval, c->op, evmax);
+                           cfg->samples + 2 * cfg->n_train, cfg->n_eval, op, evmax);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(th.data(), theta, NP * sizeof(float), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(hist.data(), loss_hist, cfg->steps * sizeof(float), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(em.data(), evmax, 2 * n_eval_blocks * sizeof(float), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        e = hipMemcpyAsync(res.data(), theta, nres * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = es;
     float ms = 0.f;
     hipEventElapsedTime(&ms, ev0, ev1);
     hipEventDestroy(ev0);
@@ -731,6 +739,7 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
         set_error(std::string("m1_mlp_train: ") + hipGetErrorString(e));
         return int(M1_EDEVICE);
     }
+    const float *hist = res.data() + NP, *em = hist + cfg->steps;
     double L = 0;
     const long tail = std::min<long>(100, cfg->steps);
     for (long s = cfg->steps - tail; s < cfg->steps; ++s) L += hist[s];
@@ -742,7 +751,9 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
         rep->max_rel_err_R = std::max<double>(rep->max_rel_err_R, em[2 * b + 1]);
     }
     rep->seconds = ms * 1e-3;
-    c->mlp_theta = th;   // packed device copy already holds the trained network
+    std::copy(res.begin(), res.begin() + NP, th.begin());
+    c->op = op;
+    c->mlp_theta.swap(th);   // packed device copy already holds the trained network
     return 0;
 }
 

@@ -1,5 +1,6 @@
-"""Batch gradient of the opacity network at block counts that end inside,
-at and past the reduction's load depth and quarters, against the oracle."""
+"""Training of the opacity network: the batch gradient at block counts that
+end inside, at and past the reduction's load depth and quarters, against the
+oracle, and the start of a run from the table's statistics."""
 import numpy as np
 import pytest
 import torch
@@ -46,3 +47,38 @@ def test_gradient_over_block_counts(orc, blocks):
         assert err <= 1e-4, (name, err)
         off += k
     say(f"  gradient over {blocks} blocks: largest rel-L2 of a layer {worst:.2e}")
+
+
+@pytest.mark.parametrize("shape", [(2, 2), (2, 5), (7, 3), (128, 128), (61, 130)])
+def test_start_from_table_statistics(shape):
+    """Normalisation (mean and standard deviation of each table) and the
+    shortcut and output bias a run starts from (the table's least-squares
+    plane), read back after one step whose learning rate, 1e-30, moves no
+    float32 parameter but a zero: normalisation to 1e-9 (the variance is a difference of
+    FP64 sums), plane to four float32 roundings of its largest coefficient."""
+    from paper_2606_26268_amd import m1
+    nr, nt = shape
+    rng = np.random.default_rng(nr * 1000 + nt)
+    u, v = np.linspace(-1, 1, nr), np.linspace(-1, 1, nt)
+    tab = I.make_table(nr, nt)
+    for k, c in (("log10_kP", (0.7, -1.3)), ("log10_kR", (-0.4, 2.1))):
+        tab[k] = np.ascontiguousarray((3.0 + c[0] * u[None, :] + c[1] * v[:, None]
+                                       + 0.3 * rng.normal(size=(nt, nr))).astype(np.float32))
+    p = I.make_uniform(I.CARTESIAN, (64, 1, 1), 1)
+    p.opacity = tab
+    s = m1.Solver(p, "p64")
+    th0 = I.mlp_init(7)
+    smp = torch.from_numpy(I.mlp_samples(64 + 64, 3)).to("cuda")
+    m1.m1_mlp_train(s.ctx, smp, 64, 64, th0, batch=64, steps=1, lr=1e-30, lr_final=1e-30)
+    th, norm = m1.m1_mlp_get(s.ctx)
+    s.close()
+    X1, X0 = np.meshgrid(v, u, indexing="ij")
+    A = np.stack([np.ones(X0.size), X0.ravel(), X1.ravel()], axis=1)
+    for o, k in enumerate(("log10_kP", "log10_kR")):
+        T = tab[k].astype(np.float64).ravel()
+        assert np.allclose(norm[2 * o:2 * o + 2], (T.mean(), T.std()), rtol=1e-9, atol=0)
+        c = np.linalg.lstsq(A, (T - T.mean()) / T.std(), rcond=None)[0]
+        got = np.array([th[4480 + o], th[4482 + 2 * o], th[4483 + 2 * o]], dtype=np.float64)
+        assert np.abs(got - c).max() <= 4 * 2.0 ** -24 * np.abs(c).max(), (got, c)
+    moved = th[:4480] != np.asarray(th0, np.float32)[:4480]      # biases of exactly zero may, by the rate
+    assert (th0[:4480][moved] == 0).all()
