@@ -17,8 +17,9 @@
 // issue-bound and a memory-bound kernel.  A second-order step, split -> fused:
 // 256^3 FP32 1363 -> 1024 us, 128^3 FP32 166 -> 113 us and FP64 304 -> 220 us,
 // 192x96x192 FP32 298 -> 240 us (constant opacities) and 310 -> 286 us (table),
-// 128^3 FP32 power law 185 -> 151 us, 2D 1000^2 FP64 187 -> 158 us, 300x200 shell
-// with the table 24.0 -> 19.9 us, 1D 2000 cells 17.3 -> 13.8 us.
+// 128^3 FP32 power law 185 -> 151 us, 1D 2000 cells 17.3 -> 13.8 us, 2D 1000^2 FP64
+// 187 -> 153 us and in tiles 88 us, 300x200 shell with the table, FP32, 24.0 ->
+// 19.8 and in tiles 16.0 us, 300^2 beam with LimO3 in FP64 38 -> 33 -> 25.7 us.
 //
 // Covers gray states with constant, power-law and tabulated opacities, in 1D
 // and 2D with every variant, in 3D with the default scheme and, in FP64 with
@@ -81,8 +82,14 @@ __global__ void __launch_bounds__(256) k_stage(StageArgs<R> a)
 template <typename R, int GEOM, int TYB, bool CONST_OPAC>
 __global__ void __launch_bounds__((Tile<TYB>::NT), (sizeof(R) == 4 ? 4 : (CONST_OPAC ? 3 : 2))) k_stage3d(StageArgs<R> a)
 {
-    transport_tile<R, GEOM, false, TYB, false>(a.t, a.nz_chunk, a.tiles_x, a.tiles_y, a.nblocks, a.cus,
+    transport_tile<R, 3, GEOM, false, TYB, false>(a.t, a.nz_chunk, a.tiles_x, a.tiles_y, a.nblocks, a.cus,
                                                SolveCell<R, CONST_OPAC>{});
+}
+
+template <typename R, int GEOM, bool GENERAL, bool LIMO3, bool CONST_OPAC>
+__global__ void __launch_bounds__(256, (sizeof(R) == 4 ? 4 : 2)) k_stage2d(StageArgs<R> a)
+{
+    transport_tile<R, 2, GEOM, GENERAL, 8, LIMO3>(a.t, 1, a.tiles_x, a.tiles_y, a.nblocks, 1, SolveCell<R, CONST_OPAC>{});
 }
 
 template <typename R, int GEOM, int TYB, bool CONST_OPAC>
@@ -106,6 +113,20 @@ static void launch_geom(m1_ctx *c, StageArgs<R> &a)
             if (launch_tile<R, GEOM, 16, CONST_OPAC>(c, a, 2)) return;
         }
         launch_tile<R, GEOM, 8, CONST_OPAC>(c, a, 0);
+        return;
+    }
+    if (tiled_2d(c)) {
+        const TileShape s = tile_shape_2d(c);
+        a.tiles_x = s.tiles_x;
+        a.tiles_y = s.tiles_y;
+        a.nblocks = s.nblocks;
+        const dim3 grid(s.launched), block(256);
+        if (a.t.limo3)
+            hipLaunchKernelGGL((k_stage2d<R, GEOM, true, true, CONST_OPAC>), grid, block, 0, c->stream, a);
+        else if (general_transport(c, a.t))
+            hipLaunchKernelGGL((k_stage2d<R, GEOM, true, false, CONST_OPAC>), grid, block, 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((k_stage2d<R, GEOM, false, false, CONST_OPAC>), grid, block, 0, c->stream, a);
         return;
     }
     const long N = long(c->n[0]) * c->n[1];

@@ -51,7 +51,23 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     k_transport3d(TArgs<R> a, int nz_chunk, int tiles_x, int tiles_y, int nblocks, int cus)
 {
     select_group(a);
-    transport_tile<R, GEOM, GENERAL, TYB, LIMO3>(a, nz_chunk, tiles_x, tiles_y, nblocks, cus, StoreCell<R>{a.out, a.out_fs});
+    transport_tile<R, 3, GEOM, GENERAL, TYB, LIMO3>(a, nz_chunk, tiles_x, tiles_y, nblocks, cus, StoreCell<R>{a.out, a.out_fs});
+}
+
+// 2D: one 32 x 8 tile a block.  What bounds it: FP32 memory (1000^2 cells:
+// 18.4 us, 36 bytes a cell at 2.0 TB/s; a large copy takes 7.5 us for them) and
+// the chain load - slopes - faces - update behind three barriers, with six blocks
+// on a compute unit to overlap them; FP64 issue and that chain, three blocks on a
+// unit (52.6 KB of LDS each).  Against a thread per cell, which computed every
+// face twice and every slope three times: 1000^2 cells FP32 30.3 -> 18.4 us, FP64
+// 66.6 -> 37.9 us, LimO3 FP32 33.1 -> 25.9 us; 300 x 200 FP32 6.1 -> 5.3 us, FP64
+// 7.8 -> 6.3 us.
+template <typename R, int GEOM, bool GENERAL, bool LIMO3>
+__global__ void __launch_bounds__(256, (sizeof(R) == 4 ? 4 : (LIMO3 ? 2 : 3)))
+    k_transport2d(TArgs<R> a, int tiles_x, int tiles_y, int nblocks)
+{
+    select_group(a);
+    transport_tile<R, 2, GEOM, GENERAL, 8, LIMO3>(a, 1, tiles_x, tiles_y, nblocks, 1, StoreCell<R>{a.out, a.out_fs});
 }
 
 // Launch with tile height TYB; with max_rounds > 0, only if the launch then
@@ -106,6 +122,24 @@ static hipError_t launch_t(m1_ctx *c, double dt, const Metric<R> &met, const voi
         }
 #undef M1_T3D_ANY
 #undef M1_T3D
+        return hipGetLastError();
+    }
+    if (tiled_2d(c)) {
+        const bool var = general_transport(c, a);
+        const TileShape s = tile_shape_2d(c);
+#define M1_T2D(GM, V, L) \
+    hipLaunchKernelGGL((k_transport2d<R, GM, V, L>), dim3(s.launched, ngrp), dim3(256), 0, c->stream, a, s.tiles_x, s.tiles_y, s.nblocks)
+#define M1_T2D_ANY(GM)                  \
+    if (a.limo3) M1_T2D(GM, true, true);  \
+    else if (var) M1_T2D(GM, true, false); \
+    else M1_T2D(GM, false, false)
+        switch (c->geom) {
+        case M1_CARTESIAN: M1_T2D_ANY(M1_CARTESIAN); break;
+        case M1_CYLINDRICAL: M1_T2D_ANY(M1_CYLINDRICAL); break;
+        default: M1_T2D_ANY(M1_SPHERICAL); break;
+        }
+#undef M1_T2D_ANY
+#undef M1_T2D
         return hipGetLastError();
     }
     dim3 block(256), grid(unsigned((N + 255) / 256), ngrp);

@@ -240,7 +240,8 @@ struct StoreCell {
     }
 };
 
-// One cell of a 1D or 2D grid per thread (blocks of 256 threads).
+// One cell of a 1D grid, or of a 2D grid too thin for the tiles (tiled_2d), per
+// thread (blocks of 256 threads).
 template <typename R, int NDIM, int GEOM, class Fin>
 __device__ __forceinline__ void transport_cell(const TArgs<R> &a, const Fin &fin)
 {
@@ -273,7 +274,7 @@ __device__ __forceinline__ void transport_cell(const TArgs<R> &a, const Fin &fin
 }
 
 // ---------------------------------------------------------------------------
-// 3D tiled kernel: a block owns a TX x TY column of cells (Tile below) and
+// Tiled kernels.  3D: a block owns a TX x TY column of cells (Tile below) and
 // marches along z
 // over a chunk of planes.  Per plane: (1) the state with a two-cell halo in
 // x and y (cross-shaped, no corners) is staged in LDS; (2) van Leer slopes
@@ -282,7 +283,8 @@ __device__ __forceinline__ void transport_cell(const TArgs<R> &a, const Fin &fin
 // and y face of the tile is computed once from the two donor states and
 // slopes (faces of both directions in one flat pass, direction chosen at run
 // time), and the z face above the plane from a per-thread register window
-// of four planes and the z slopes of planes k and k+1; (4) the update.
+// of four planes and the z slopes of planes k and k+1; (4) the update.  2D: a
+// block owns one tile and takes it through the same steps without the z part.
 // ---------------------------------------------------------------------------
 // Tile of a block: TX x TY cells, one thread per cell, TY = 8 (256 threads)
 // or 16 (512 threads).  The taller tile computes 4 % fewer halo faces and
@@ -307,7 +309,7 @@ struct Tile {
     static_assert(S2 <= NT && F2 <= NT && NHALO <= NT, "one task per thread in pass 2, one halo cell at most");
 };
 
-template <typename R, int GEOM, bool GENERAL, int TYB, bool LIMO3, class Fin>
+template <typename R, int NDIM, int GEOM, bool GENERAL, int TYB, bool LIMO3, class Fin>
 __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, int tiles_x, int tiles_y, int nblocks,
                                                int cus, const Fin &fin)
 {
@@ -380,7 +382,7 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         const TArgs<R> &g = first_argument<TArgs<R>>();
         ghost_fix(g, 0, i, n0, q);
         ghost_fix(g, 1, j, n1, q);
-        ghost_fix(g, 2, kk, n2, q);
+        if (NDIM == 3) ghost_fix(g, 2, kk, n2, q);
     };
     auto fix_halo = [&](R q[4]) {
         if (!GENERAL || !a.special) return;
@@ -443,7 +445,7 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     const int bz0 = a.bc[2][0], bz1 = a.bc[2][1];
     // cell c of plane kk (mapped) and its optical depth
     auto loadp = [&](int kk, int c, R q[4], R &t) {
-        const int lin = map_index(kk, n2, bz0, bz1) * plane + c;
+        const int lin = NDIM == 3 ? map_index(kk, n2, bz0, bz1) * plane + c : c;
         load4(a, lin, q);
         t = a.tau[lin];
     };
@@ -461,7 +463,12 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     // k, they arrive while its faces are computed.
     R W0[4], W1[4], T0, T1, Fz0[4], Fz1[4], Sz0[4], Sz1[4], Hq[4], Ht = R(0);
     Centre<R> C0, C1;                   // f-fix quantities of plane k and k + 1
-    {
+    if constexpr (NDIM == 2) {
+        loadp(0, col, W0, T0);
+        if (tid < NHALO) loadp(0, hcol, Hq, Ht);
+        fix_col(0, W0);
+        C0 = centre_of(W0);
+    } else {
         R Q0[4], Qm[4], Szm[4], Tm, Tx;
         loadp(z0 - 2, col, Q0, Tx);
         loadp(z0 - 1, col, Qm, Tm);
@@ -500,11 +507,11 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     // 1 % with several; FP64, two 32 x 8 blocks per unit: 1-1.5 %).  The
     // general kernels run other block counts per unit; for them the
     // alternation did not pay (1-6 % slower).
-    constexpr bool ALTERNATE = !GENERAL;
+    constexpr bool ALTERNATE = NDIM == 3 && !GENERAL;
     const int prio_grp = (int(blockIdx.x) / cus) & 1;
     // One plane: Wa, Wb are planes k and k + 1 of the window, Wc takes k + 2;
     // Fa, Fb the fluxes below and above, Sa, Sb the (upper-face) z slopes of
-    // planes k and k + 1.
+    // planes k and k + 1.  In 2D the one plane there is, without window or z faces.
     auto step = [&](int k, const R (&Wa)[4], const R (&Wb)[4], R (&Wc)[4], const R (&Fa)[4], R (&Fb)[4],
                     const R (&Sa)[4], R (&Sb)[4], const Centre<R> &Ca, Centre<R> &Cb, R Ta, R Tb, R &Tc) {
         if constexpr (ALTERNATE) {
@@ -514,8 +521,10 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
                 __builtin_amdgcn_s_setprio(0);
         }
         // the plane entering the window
-        loadp(k + 2, col, Wc, Tc);
-        fix_col(k + 2, Wc);
+        if constexpr (NDIM == 3) {
+            loadp(k + 2, col, Wc, Tc);
+            fix_col(k + 2, Wc);
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v) sq[v][ly + 2][lx + 2] = Wa[v];
         st[ly + 1][lx + 2] = Ta;
@@ -531,7 +540,7 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
                 (&scf[0][0][0])[hq - HX] = ch.f2;
                 (&scf[1][0][0])[hq - HX] = ch.ie;
             }
-            if (k + 1 < z1) loadp(k + 1, hcol, Hq, Ht);
+            if (NDIM == 3 && k + 1 < z1) loadp(k + 1, hcol, Hq, Ht);
         }
         __syncthreads();
 
@@ -582,7 +591,9 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         // z slope(s) of plane k+1 (LimO3: Sb its upper-face slope, Sl its
         // lower-face one)
         R Sl[4];
-        if constexpr (LIMO3)
+        if constexpr (NDIM == 2)
+            ;
+        else if constexpr (LIMO3)
             limo3_slopes4(Wa, Wb, Wc, rz[k + 3], Sl, Sb);
         else
             slopes4(Wa, Wb, Wc, rz[k + 3], Sb);
@@ -635,8 +646,10 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         }
 
         // z face above the plane from the register window
-        Cb = centre_of(Wb);
-        face_flux_s<R>(2, Wa, Wb, Sa, LIMO3 ? Sl : Sb, Ca, Cb, hpz[k + 2], hmz[k + 3], Ta + Tb, Fb, recon, riemann);
+        if constexpr (NDIM == 3) {
+            Cb = centre_of(Wb);
+            face_flux_s<R>(2, Wa, Wb, Sa, LIMO3 ? Sl : Sb, Ca, Cb, hpz[k + 2], hmz[k + 3], Ta + Tb, Fb, recon, riemann);
+        }
         // The empty statement hides that the cell's index is the same in every
         // plane: the compiler otherwise hoists a 64-bit lane address for each
         // of the cell's arrays out of the loop and spills.
@@ -654,17 +667,24 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
             const R tr1 = GEOM == M1_CARTESIAN ? dtc : sux[2][lx];
             const R ayl = suy[0][ly] * tr1, ayh = same_area<GEOM, 1> ? ayl : suy[1][ly] * tr1;
             const R tr2 = GEOM == M1_SPHERICAL ? suy[2][ly] * tr1 : dtc;
-            const R azl = a.m.alo[2][k] * tr2, azh = same_area<GEOM, 2> ? azl : a.m.ahi[2][k] * tr2;
+            const R azl = NDIM == 3 ? a.m.alo[2][k] * tr2 : R(0);
+            const R azh = NDIM == 2 || same_area<GEOM, 2> ? azl : a.m.ahi[2][k] * tr2;
             const R ct = GEOM == M1_SPHERICAL ? suy[3][ly] : R(0);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 acc[v] = face_diff<same_area<GEOM, 0>>(axl, axh, ss[v][xs], ss[v][xr]) +
                          face_diff<same_area<GEOM, 1>>(ayl, ayh, sfy[v][ly][lx], sfy[v][ly + 1][lx]) +
-                         face_diff<same_area<GEOM, 2>>(azl, azh, Fa[v], Fb[v]);
+                         (NDIM == 3 ? face_diff<same_area<GEOM, 2>>(azl, azh, Fa[v], Fb[v]) : R(0));
+            if (NDIM == 2 && a.ign[2]) ignorable_div<R, 2>(a, Wa, Ca, tr2, acc);
             finish_cell<R, GEOM>(a, Wa, Ca, acc, tr1, ct, Us);
             fin(in, Us, Ta, i, j, k, base, cell);
         }
     };
+    if constexpr (NDIM == 2) {
+        R Wn[4], Tn;
+        step(0, W0, W1, Wn, Fz0, Fz1, Sz0, Sz1, C0, C1, T0, T1, Tn);
+        return;
+    }
     for (int k = z0; k < z1; ++k) {
         R Wn[4], Tn;
         step(k, W0, W1, Wn, Fz0, Fz1, Sz0, Sz1, C0, C1, T0, T1, Tn);
@@ -747,6 +767,33 @@ inline TileShape tile_shape(const m1_ctx *c, const void *kern, unsigned ngrp)
     s.nblocks = s.tiles_x * s.tiles_y * ((c->n[2] + s.nz - 1) / s.nz);
     s.launched = ((s.nblocks + 7) / 8) * 8;
     return s;
+}
+
+// 2D: one 32 x 8 tile a block.
+inline TileShape tile_shape_2d(const m1_ctx *c)
+{
+    using T = Tile<8>;
+    TileShape s;
+    s.tiles_x = (c->n[0] + T::TX - 1) / T::TX;
+    s.tiles_y = (c->n[1] + T::TY - 1) / T::TY;
+    s.nz = 1;
+    s.rounds = 0;
+    s.nblocks = s.tiles_x * s.tiles_y;
+    s.launched = ((s.nblocks + 7) / 8) * 8;
+    return s;
+}
+
+// Whether a 2D grid takes the tiles: where more than half of their threads own
+// a cell.  A tile computes each face and slope once (a thread per cell computes
+// two faces and three slopes per direction), so the sides meet at half its
+// threads idle.  Transport, a thread per cell -> tiles, FP32 and FP64: 20 x
+// 200,000 cells (0.63 of the threads) 115 -> 91 and 258 -> 224 us, 16 x 200,000
+// (0.5) 93 -> 91 and 199 -> 214 us, 200,000 x 3 (0.38) 22 -> 25 and 45 -> 56 us.
+inline bool tiled_2d(const m1_ctx *c)
+{
+    if (c->ndim != 2) return false;
+    const TileShape s = tile_shape_2d(c);
+    return 2.0 * c->n[0] * c->n[1] > 256.0 * s.tiles_x * s.tiles_y;
 }
 
 // Transport arguments for the radiation arrays rad (the bound state's if null)
