@@ -239,6 +239,18 @@ static m1_status upload_metric(m1_ctx *c, const HostMetric &M)
     return M1_OK;
 }
 
+// Record of each cell of a bound table (tab: kappa_P then kappa_R [nt][nr]):
+// kappa_P, then kappa_R, at its four nodes.  One thread a cell.
+__global__ void __launch_bounds__(256) k_table_cells(const float *tab, int nr, int nt, float *cells)
+{
+    const size_t t = size_t(blockIdx.x) * 256 + threadIdx.x, n = size_t(nr) * nt;
+    if (t >= size_t(nr - 1) * (nt - 1)) return;
+    const size_t o = t / (nr - 1) * nr + t % (nr - 1);
+    float4 *rec = reinterpret_cast<float4 *>(cells) + 2 * t;
+    rec[0] = make_float4(tab[o], tab[o + 1], tab[o + nr], tab[o + nr + 1]);
+    rec[1] = make_float4(tab[n + o], tab[n + o + 1], tab[n + o + nr], tab[n + o + nr + 1]);
+}
+
 static size_t elem_size(const m1_ctx *c) { return c->par.precision == M1_F32 ? 4 : 8; }
 
 static long ncells(const m1_ctx *c) { return (long)c->n[0] * c->n[1] * c->n[2]; }
@@ -514,32 +526,31 @@ m1_status m1_set_opacity_table(m1_ctx *c, int nr, int nt, double lr0, double lr1
     // kappa_R, so that a lookup reads two 16-byte words instead of
     // gathering eight values from four rows
     const size_t ncell = size_t(nr - 1) * (nt - 1), off = (2 * n + 3) & ~size_t(3);
-    std::vector<float> host(off + 8 * ncell, 0.0f);
+    std::vector<float> host(2 * n);
     std::copy(kP, kP + n, host.begin());
     std::copy(kR, kR + n, host.begin() + n);
-    for (int j = 0; j + 1 < nt; ++j)
-        for (int i = 0; i + 1 < nr; ++i) {
-            const size_t o = size_t(j) * nr + i;
-            float *r = &host[off + 8 * (size_t(j) * (nr - 1) + i)];
-            const size_t node[4] = {o, o + 1, o + nr, o + nr + 1};
-            for (int q = 0; q < 4; ++q) {
-                r[q] = kP[node[q]];
-                r[4 + q] = kR[node[q]];
-            }
-        }
+    double norm[4];
+    float lin[2][3];
+    mlp_table_stats(kP, kR, nr, nt, norm, lin);
     // the new table is uploaded before the old one is released: on failure
     // the context keeps its previous opacity source unchanged
     float *tab = nullptr;
-    hipError_t e = device_alloc(reinterpret_cast<void **>(&tab), host.size() * sizeof(float));
+    hipError_t e = device_alloc(reinterpret_cast<void **>(&tab), (off + 8 * ncell) * sizeof(float));
     if (e != hipSuccess) return fail(M1_ENOMEM, "m1_set_opacity_table: allocation failed");
-    e = hipMemcpy(tab, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice);
+    e = hipMemcpy(tab, host.data(), 2 * n * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_table_cells, dim3(unsigned((ncell + 255) / 256)), dim3(256), 0, c->stream, tab, nr,
+                           nt, tab + off);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) {
         hipFree(tab);
         return hip_fail(e, "m1_set_opacity_table: upload");
     }
     if (c->table_dev) hipFree(c->table_dev);
     c->table_dev = tab;
-    mlp_table_stats(kP, kR, nr, nt, c->tab_norm, c->tab_lin);
+    std::copy(norm, norm + 4, c->tab_norm);
+    std::copy(&lin[0][0], &lin[0][0] + 6, &c->tab_lin[0][0]);
     c->op.kind = OPK_TABLE;
     c->op.nr = nr;
     c->op.nt = nt;

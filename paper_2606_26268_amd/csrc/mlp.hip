@@ -578,57 +578,51 @@ __global__ void __launch_bounds__(256) k_mlp_eval(const float *pk, const float *
 // host driver
 // ---------------------------------------------------------------------------
 
-// Sums of four interleaved parts (a single chain of additions takes four times
-// as long).
-template <typename F>
-static inline double sum4(long n, F f)
-{
-    double s[4] = {0, 0, 0, 0};
-    long q = 0;
-    for (; q + 4 <= n; q += 4)
-        for (int e = 0; e < 4; ++e) s[e] += f(q + e);
-    for (; q < n; ++q) s[0] += f(q);
-    return (s[0] + s[1]) + (s[2] + s[3]);
-}
-
 // mean / std of each table and the least-squares plane t = b + w0 x0 + w1 x1
-// (normalised units) used to initialise the linear shortcut.  Taken when a
-// table is bound, where its values are at hand: a training run took 76 us to
-// read a 128 x 128 table back and 81 us for these sums.
+// (normalised units) used to initialise the linear shortcut, from one pass over
+// the differences from the first node (four interleaved sums each: one chain
+// of additions takes four times as long).  Taken when a table is bound, where
+// its values are at hand: a training run took 76 us to read a 128 x 128 table back
+// and 81 us for its sums.
 void mlp_table_stats(const float *kP, const float *kR, int nr, int nt, double norm[4], float lin[2][3])
 {
-    const long n = (long)nr * nt;
+    const double n = double(nr) * nt, di = 2.0 / (nr - 1), dj = 2.0 / (nt - 1);
+    double f1 = 0, f2 = 0, g1 = 0, g2 = 0;      // node coordinates: sums and sums of squares
+    for (int i = 0; i < nr; ++i) f1 += di * i - 1.0, f2 += (di * i - 1.0) * (di * i - 1.0);
+    for (int j = 0; j < nt; ++j) g1 += dj * j - 1.0, g2 += (dj * j - 1.0) * (dj * j - 1.0);
     for (int o = 0; o < 2; ++o) {
         const float *T = o ? kR : kP;
-        const double s = sum4(n, [&](long q) { return double(T[q]); });
-        const double s2 = sum4(n, [&](long q) { return double(T[q]) * T[q]; });
-        const double mean = s / n, var = s2 / n - mean * mean;
-        const double sd = var > 0 ? std::sqrt(var) : 1.0, inv = 1.0 / sd;
-        norm[2 * o] = mean;
-        norm[2 * o + 1] = sd;
-        // normal equations of the plane fit on the node grid, row by row
-        const double di = 2.0 / (nr - 1), dj = 2.0 / (nt - 1);
-        const double f1 = sum4(nr, [&](long i) { return di * i - 1.0; });
-        const double f2 = sum4(nr, [&](long i) { return (di * i - 1.0) * (di * i - 1.0); });
-        double A[3][3] = {{0}}, b[3] = {0};
+        const double ref = T[0];
+        double S = 0, S2 = 0, SF = 0, SG = 0;   // sums of d, d^2, d x0, d x1
         for (int j = 0; j < nt; ++j) {
             const float *row = T + (long)j * nr;
-            const double g = dj * j - 1.0;
-            const double t0 = sum4(nr, [&](long i) { return (row[i] - mean) * inv; });
-            const double t1 = sum4(nr, [&](long i) { return (row[i] - mean) * inv * (di * i - 1.0); });
-            b[0] += t0;
-            b[1] += t1;
-            b[2] += g * t0;
-            A[0][0] += nr;
-            A[0][1] += f1;
-            A[0][2] += g * nr;
-            A[1][1] += f2;
-            A[1][2] += g * f1;
-            A[2][2] += g * g * nr;
+            double s[4] = {0, 0, 0, 0}, q[4] = {0, 0, 0, 0}, w[4] = {0, 0, 0, 0};
+            int i = 0;
+            for (; i + 4 <= nr; i += 4)
+                for (int e = 0; e < 4; ++e) {
+                    const double d = row[i + e] - ref;
+                    s[e] += d;
+                    q[e] += d * d;
+                    w[e] += d * (di * (i + e) - 1.0);
+                }
+            for (; i < nr; ++i) {
+                const double d = row[i] - ref;
+                s[0] += d;
+                q[0] += d * d;
+                w[0] += d * (di * i - 1.0);
+            }
+            const double r = (s[0] + s[1]) + (s[2] + s[3]);
+            S += r;
+            S2 += (q[0] + q[1]) + (q[2] + q[3]);
+            SF += (w[0] + w[1]) + (w[2] + w[3]);
+            SG += (dj * j - 1.0) * r;
         }
-        A[1][0] = A[0][1];
-        A[2][0] = A[0][2];
-        A[2][1] = A[1][2];
+        const double dm = S / n, var = S2 / n - dm * dm, sd = var > 0 ? std::sqrt(var) : 1.0;
+        norm[2 * o] = ref + dm;
+        norm[2 * o + 1] = sd;
+        // normal equations of the plane fit on the node grid
+        double A[3][3] = {{n, f1 * nt, g1 * nr}, {f1 * nt, f2 * nt, f1 * g1}, {g1 * nr, f1 * g1, g2 * nr}};
+        double b[3] = {(S - n * dm) / sd, (SF - dm * f1 * nt) / sd, (SG - dm * g1 * nr) / sd};
         for (int piv = 0; piv < 3; ++piv)          // Gaussian elimination (SPD, no pivoting)
             for (int r = piv + 1; r < 3; ++r) {
                 const double m = A[r][piv] / A[piv][piv];
