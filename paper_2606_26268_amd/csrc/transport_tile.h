@@ -504,7 +504,7 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     // (FP32, measured on the 192x96x192 grid), and the second then ran alone
     // at half occupancy.  The two alternate their wave priority every plane
     // and stay level (FP32: 3-4 % faster transport with one round of blocks,
-    // 1 % with several; FP64, two 32 x 8 blocks per unit: 1-1.5 %).  The
+    // 1 % with several; FP64, measured with two blocks per unit: 1-1.5 %).  The
     // general kernels run other block counts per unit; for them the
     // alternation did not pay (1-6 % slower).
     constexpr bool ALTERNATE = NDIM == 3 && !GENERAL;
