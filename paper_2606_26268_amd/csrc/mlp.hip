@@ -44,33 +44,19 @@ __host__ __device__ __forceinline__ int frag_slot(int m, int k)
 }
 
 // The inference form's LDS image in the packed network, from the flat
-// parameters: the split fragments of A2 = -2 s 2^-e W2, one W2 element per
-// thread, and the layer-1, layer-2 start and output entries (mlp_image_entry).
-// e is the smallest power of two, from 0 to 15, that brings 2 s max |W2| under
-// 2^15; every block finds it for itself.  16 blocks of 256 threads.
+// parameters: the split fragments of A2 = s W2 (s = MLP_TANH_SCALE), one W2
+// element per thread, and the layer-1, bias and output entries
+// (mlp_image_entry).  16 blocks of 256 threads.
 __global__ void __launch_bounds__(256) k_mlp_pack_infer(const float *theta, float *pk)
 {
-    __shared__ float top[4];
-    float m = 0.0f;
-    for (int q = threadIdx.x; q < 4096; q += 256) m = fmaxf(m, fabsf(theta[P_W2 + q]));
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = m;
-    __syncthreads();
-    m = 2.0f * MLP_TANH_SCALE * fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]));
-    float se = MLP_TANH_SCALE;
-    for (int e = 0; e < 15 && m > 32768.0f; ++e) {
-        m *= 0.5f;
-        se *= 0.5f;
-    }
     const int t = blockIdx.x * 256 + threadIdx.x;
     const int u = t >> 6, k = t & 63;
     MlpShared &img = *reinterpret_cast<MlpShared *>(pk + MLP_OFF_IMG);
-    _Float16 h, l;
-    split_a2(theta[P_W2 + t], se, h, l);
-    reinterpret_cast<_Float16 *>(&img.w2[0][0][0][0])[frag_slot(u, k)] = h;
-    reinterpret_cast<_Float16 *>(&img.w2[1][0][0][0])[frag_slot(u, k)] = l;
-    mlp_image_entry(theta + P_W1, theta + P_B1, theta + P_W2, theta + P_B2, theta + P_W3, se, img, t);
+    const float v = MLP_TANH_SCALE * theta[P_W2 + t];
+    const __bf16 h = to_bf16(v);
+    reinterpret_cast<__bf16 *>(&img.w2[0][0][0][0])[frag_slot(u, k)] = h;
+    reinterpret_cast<__bf16 *>(&img.w2[1][0][0][0])[frag_slot(u, k)] = to_bf16(v - float(h));
+    mlp_image_entry(theta + P_W1, theta + P_B1, theta + P_B2, theta + P_W3, img, t);
 }
 
 // One parameter's entries in the packed network (all but the inference image).

@@ -19,19 +19,17 @@
 namespace m1 {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // LDS image of the inference form (see the inference section below); the
 // packed network holds it at MLP_OFF_IMG, 16-byte words copied as they are
 struct MlpShared {
-    f16x8 w2[2][2][4][64];    // A2 fragments [hi, lo][mt][ks][lane], 16 KiB
+    bf16x8 w2[2][2][4][64];   // A2 fragments [hi, lo][mt][ks][lane], 16 KiB
     bf16x8 w1[2][64];         // layer-1 A operand: [mt][lane]
-    bf16x8 c2[2][64];         // layer-2 start as an A operand [mt][lane]: K slots 0..2 its three bfloat16 pieces
+    bf16x8 c2[2][64];         // s b2 as an A operand [mt][lane]: K slots 0..2 its three bfloat16 pieces
     float2 ep[2][2][16];      // [g][mt][i]: -2 W3[0], -2 W3[1] of the slot's unit
     float w3sum[2];           // sum over units of W3[0], W3[1]
-    float rscale;             // 2^-e: the hidden values enter layer 2 as 2^e r1
-    float pad;                // to a whole number of 16-byte words
+    float pad[2];             // to a whole number of 16-byte words
 };
 static_assert(sizeof(MlpShared) % 16 == 0, "MlpShared is staged in 16-byte words");
 
@@ -46,13 +44,12 @@ static_assert(sizeof(MlpShared) % 16 == 0, "MlpShared is staged in 16-byte words
 //   [512, 2560)   W2 hi fragments: bf16 [mt 2][ks 4][lane 64][8]
 //   [2560, 4608)  W2 lo fragments, same order
 //   [4608, 9860)  the inference form's LDS image (MlpShared below), staged
-//                 by every block as it is: A2 hi and lo fragments in half
-//                 precision (A2 = -2 s 2^-e W2, s = MLP_TANH_SCALE, same
-//                 order as W2), the layer-1 and layer-2 start operands and
-//                 the output weights
+//                 by every block as it is: A2 hi and lo fragments
+//                 (A2 = s W2, s = MLP_TANH_SCALE, same order as W2), the
+//                 layer-1 and bias operands and the output weights
 // (the image serves the inference form below, whose second layer delivers
-// the scaled pre-activation s (W2 h1 + b2) directly; it is derived on the
-// device from the flat parameters whenever they change)
+// the scaled pre-activation s (W2 h1 + b2) = A2 h1 + s b2 directly; it is
+// derived on the device from the flat parameters whenever they change)
 constexpr int MLP_OFF_W1 = 0, MLP_OFF_B1 = 128, MLP_OFF_B2 = 192, MLP_OFF_W3 = 256;
 constexpr int MLP_OFF_B3 = 384, MLP_OFF_WS = 386, MLP_OFF_NORM = 390;
 constexpr int MLP_OFF_W2HI = 512, MLP_OFF_W2LO = 2560;
@@ -117,53 +114,39 @@ __device__ __forceinline__ void mlp_inputs(const OpacityParams &op, float rho, f
 // B operand: no hidden value changes lanes.
 //
 // tanh is evaluated as 1 - 2 r with r = 1 / (1 + 2^z), z = 2 log2(e) x =
-// s x.  The factor s is folded into the staged first-layer weights, and both
-// it and h1 = 1 - 2 r1 into the second layer, which takes r1 itself:
-//   z2 = s (W2 h1 + b2) = s (b2 + sum W2) + (-2 s W2) r1.
-// Weights and r1 are split into a half-precision high part and remainder, 22
-// significant bits in all (hi hi + hi lo + lo hi; 16 bits of a bfloat16 pair
-// left the products with the split error of r1 ~ 1/2 where h1 is small, and
-// log10 kappa five times further off).  The accumulator starts at
-// s b2 - A2 1 / 2, the sum taken over the split weights, so that h1 = 0
-// gives s b2 to FP32 rounding (one more matrix product, the start in three
-// exact bfloat16 pieces against a column of ones).  Weights too large for half
-// precision are scaled by 2^-e (e = 0 for |W2| up to 5700) and r1 by 2^e, which
-// the reciprocal's argument takes for free.  The output layer takes
-// h2 = 1 - 2 r2 as sum W3 - 2 sum W3 r2.
-// The split of a pair costs two conversions and two mixed-precision
-// multiply-adds (they read the packed high parts), where the bfloat16 split of
-// h1 took two conversions, two masks, two subtractions and the two operations
-// of h1 itself: 950 vector instructions a wavefront instead of 1090, and
-// log10 kappa within 1.7e-6 of the exact network instead of 7.8e-6.  The implicit
-// kernel gained 2 % (192x96x192: 157 -> 154 us): vector unit or matrix cores are
-// busy in 92 % of its cycles either way, and they overlap in half of the matrix
-// time only.
+// s x.  The factor s is folded into the staged first-layer weights and into
+// the second layer: its weights are A2 = s W2 (split hi + lo, packed with
+// the network) and its accumulator starts at s b2 (one more matrix product,
+// s b2 in three exact bfloat16 pieces against a column of ones), so the
+// matrix cores deliver z2 = s (W2 h1 + b2) directly; the output layer takes
+// h2 = 1 - 2 r2 as sum W3 - 2 sum W3 r2.  (Folding h1 = 1 - 2 r1 into the
+// second layer as well would save one more operation per unit, but the
+// products would then carry the split error of r1 ~ 1/2 where h1 is small:
+// measured, 3.4e-5 against 6-8e-6 in log10 kappa from the exact network on
+// random weights, five times the error.)
 // ---------------------------------------------------------------------------
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __fp16 f16x2_t __attribute__((ext_vector_type(2)));
-
-// Split two floats in [0, 2^15] into packed half-precision high parts (rounded
-// towards zero) and packed remainders: a = hi_a + lo_a + O(2^-21 a).  minus1
-// is -1 in a register: as a constant, the compiler turns the multiply-add
-// into a conversion and a subtraction.
-__device__ __forceinline__ void split_f16x2(float a, float b, float minus1, unsigned &hi, unsigned &lo)
+// tanh(z / MLP_TANH_SCALE); saturates to -1 and +1 for large |z|
+__device__ __forceinline__ float tanh_scaled(float z)
 {
-    const f16x2_t h = __builtin_amdgcn_cvt_pkrtz(a, b);
-    hi = __builtin_bit_cast(unsigned, h);
-    const float la = __builtin_fmaf(float(h[0]), minus1, a);
-    const float lb = __builtin_fmaf(float(h[1]), minus1, b);
-    lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(la, lb));
+    return __builtin_fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z)), 1.0f);
 }
 
-// Half-precision high part and remainder of a second-layer weight w = W2[u][k]
-// of a network scaled by 2^-e (se = s 2^-e): A2 = -2 se w, clamped to the
-// range of the format (no network within |W2| < 1.8e8 reaches it).
-__device__ __forceinline__ void split_a2(float w, float se, _Float16 &hi, _Float16 &lo)
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// Split two floats into packed bfloat16 high parts (round to nearest even)
+// and packed bfloat16 remainders: a = hi_a + lo_a + O(2^-18 |a|).
+__device__ __forceinline__ void split_bf16x2(float a, float b, unsigned &hi, unsigned &lo)
 {
-    const float v = __builtin_fminf(__builtin_fmaxf(-2.0f * se * w, -65504.0f), 65504.0f);
-    hi = (_Float16)v;
-    lo = (_Float16)(v - float(hi));
+    const bf16x2_t h = {to_bf16(a), to_bf16(b)};
+    hi = __builtin_bit_cast(unsigned, h);
+    // a's high part moved to the upper half by a byte permutation of the
+    // packed word (bytes 1, 0 to 3, 2; zeros below): written as a shift,
+    // the compiler re-derives it from a with one more conversion
+    const float ha = __uint_as_float(__builtin_amdgcn_perm(0u, hi, 0x01000c0cu));
+    const float hb = __uint_as_float(hi & 0xffff0000u);
+    const bf16x2_t l = {to_bf16(a - ha), to_bf16(b - hb)};
+    lo = __builtin_bit_cast(unsigned, l);
 }
 
 // Exact three-piece split v = h + m + l (bfloat16 each), returned packed as
@@ -186,13 +169,13 @@ __host__ __device__ constexpr int mlp_l1_unit(int mt, int r)
 }
 
 // Entries of the LDS image derived from the flat parameters (W1 [64][2],
-// b1 [64], W2 [64][64], b2 [64], W3 [2][64] of the flat vector; se = s 2^-e), for thread t of a
+// b1 [64], b2 [64], W3 [2][64] of the flat vector), for thread t of a
 // 4096-thread pack grid (the A2 fragments are written elsewhere): t < 128
 // the layer-1 operand, 128 <= t < 256 the bias operand, 256 <= t < 320 the
 // output weights, and the wavefront 320 <= t < 384 (which runs this branch
 // whole) the sums of W3 in a fixed order.
-__device__ __forceinline__ void mlp_image_entry(const float *W1, const float *b1, const float *W2, const float *b2,
-                                                const float *W3, float se, MlpShared &img, int t)
+__device__ __forceinline__ void mlp_image_entry(const float *W1, const float *b1, const float *b2, const float *W3,
+                                                MlpShared &img, int t)
 {
     if (t < 128) {
         // layer-1 A operand of lane l in tile mt: row l % 32, K = 8 (l / 32) + e
@@ -213,18 +196,11 @@ __device__ __forceinline__ void mlp_image_entry(const float *W1, const float *b1
         v.w = g ? bl : (bh | (bm << 16));
         img.w1[mt][l] = __builtin_bit_cast(bf16x8, v);
     } else if (t < 256) {
-        // the accumulator's start s b2 - 2^e sum A2 / 2 (over the split
-        // weights) enters through one more product, A = the start in K slots
-        // 0..2 (exact three-piece split) against B = 1 there
-        const int q = t - 128, mt = q >> 6, l = q & 63, u = 32 * mt + (l & 31);
-        double sum = 0.0;
-        for (int k = 0; k < 64; ++k) {
-            _Float16 h, r;
-            split_a2(W2[64 * u + k], se, h, r);
-            sum += double(float(h)) + double(float(r));
-        }
+        // the accumulator's start s b2 enters through one more product, A =
+        // s b2 in K slots 0..2 (exact three-piece split) against B = 1 there
+        const int q = t - 128, mt = q >> 6, l = q & 63;
         unsigned hm, hl;
-        split3_bf16(float(double(MLP_TANH_SCALE) * b2[u] - 0.5 * sum * double(MLP_TANH_SCALE / se)), hm, hl);
+        split3_bf16(MLP_TANH_SCALE * b2[32 * mt + (l & 31)], hm, hl);
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
         if (l < 32) {
             v.x = hm;              // K 0, 1: c2 hi, c2 mid
@@ -248,8 +224,7 @@ __device__ __forceinline__ void mlp_image_entry(const float *W1, const float *b1
         if (lane == 0) {
             img.w3sum[0] = s0;
             img.w3sum[1] = s1;
-            img.rscale = se / MLP_TANH_SCALE;
-            img.pad = 0.0f;
+            img.pad[0] = img.pad[1] = 0.0f;
         }
     }
 }
@@ -287,9 +262,6 @@ __device__ __forceinline__ void mlp_forward_shared(const float *p, const MlpShar
     // B operand of the bias product: 1 in K slots 0..2 (lanes of group 0)
     const bf16x8 ones = __builtin_bit_cast(bf16x8, g ? make_uint4(0u, 0u, 0u, 0u)
                                                     : make_uint4(0x3f803f80u, 0x3f80u, 0u, 0u));
-    const float rs = sh.rscale;
-    float minus1 = -1.0f;
-    asm("" : "+s"(minus1));
     f32x16 acc[2][2];
 #pragma unroll
     for (int m1 = 0; m1 < 2; ++m1) {
@@ -300,33 +272,31 @@ __device__ __forceinline__ void mlp_forward_shared(const float *p, const MlpShar
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
             const int ks = 2 * m1 + hs;
-            f16x8 bh[2], bl[2];
+            bf16x8 bh[2], bl[2];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
-                // 2^e r1 = 1 / (2^-e + 2^-e 2^z1)
-                float r[8];
+                float h[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    r[e] = __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_amdgcn_exp2f(z1[nt][8 * hs + e]), rs, rs));
+                for (int e = 0; e < 8; ++e) h[e] = tanh_scaled(z1[nt][8 * hs + e]);
                 uint4 ph, pl;
-                split_f16x2(r[0], r[1], minus1, ph.x, pl.x);
-                split_f16x2(r[2], r[3], minus1, ph.y, pl.y);
-                split_f16x2(r[4], r[5], minus1, ph.z, pl.z);
-                split_f16x2(r[6], r[7], minus1, ph.w, pl.w);
-                bh[nt] = __builtin_bit_cast(f16x8, ph);
-                bl[nt] = __builtin_bit_cast(f16x8, pl);
+                split_bf16x2(h[0], h[1], ph.x, pl.x);
+                split_bf16x2(h[2], h[3], ph.y, pl.y);
+                split_bf16x2(h[4], h[5], ph.z, pl.z);
+                split_bf16x2(h[6], h[7], ph.w, pl.w);
+                bh[nt] = __builtin_bit_cast(bf16x8, ph);
+                bl[nt] = __builtin_bit_cast(bf16x8, pl);
             }
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
-                const f16x8 ah = sh.w2[0][mt][ks][lane], al = sh.w2[1][mt][ks][lane];
+                const bf16x8 ah = sh.w2[0][mt][ks][lane], al = sh.w2[1][mt][ks][lane];
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt) {
                     const f32x16 c0 = ks == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(sh.c2[mt][lane], ones,
                                                                                          f32x16{}, 0, 0, 0)
                                               : acc[mt][nt];
-                    f32x16 t = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[nt], c0, 0, 0, 0);
-                    t = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[nt], t, 0, 0, 0);
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[nt], t, 0, 0, 0);
+                    f32x16 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[nt], c0, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[nt], t, 0, 0, 0);
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[nt], t, 0, 0, 0);
                 }
             }
         }
