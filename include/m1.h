@@ -27,7 +27,8 @@
  *     float (M1_F32); gas arrays (rho, mx, my, mz, Eg) are always double.
  *   - All work is enqueued asynchronously on the stream given by
  *     m1_set_stream (default: the null stream); no call synchronises except
- *     m1_sync, m1_diagnostics, m1_mlp_train and m1_mlp_get.
+ *     m1_sync, m1_diagnostics, m1_set_opacity_table, m1_set_opacity_mlp,
+ *     m1_mlp_train, m1_mlp_gradient and m1_mlp_get.
  *   - Every function returns an m1_status; a negative value is an error
  *     whose text m1_last_error() returns.  No call allocates device memory
  *     after m1_bind_state except m1_set_opacity_table, m1_set_opacity_mlp
@@ -245,8 +246,10 @@ m1_status m1_set_opacity_model(m1_ctx *ctx, int kind, const double *params);
  * (log10 rho + lr_off, log10 T + lt_off), clamped to the axes.  nr, nt >= 2.
  * The library keeps the tables and, for the lookup, one 32-byte record per
  * table cell with its four node values of both (device memory of about
- * 40 nr nt bytes, and as much host memory while the call runs).
- * On M1_ENOMEM or an upload error the previous opacity source is kept. */
+ * 40 nr nt bytes, and 8 nr nt bytes of host memory while the call runs).  The
+ * table is complete on the device when the call returns, for whichever stream
+ * m1_set_stream names next.  On M1_ENOMEM or an upload error the previous
+ * opacity source is kept. */
 m1_status m1_set_opacity_table(m1_ctx *ctx, int nr, int nt, double lr_min, double lr_max,
                                double lt_min, double lt_max, double lr_off, double lt_off,
                                const float *log10_kP, const float *log10_kR, double sigma);

@@ -532,8 +532,10 @@ m1_status m1_set_opacity_table(m1_ctx *c, int nr, int nt, double lr0, double lr1
     double norm[4];
     float lin[2][3];
     mlp_table_stats(kP, kR, nr, nt, norm, lin);
-    // the new table is uploaded before the old one is released: on failure
-    // the context keeps its previous opacity source unchanged
+    // the new table is complete on the device before the old one is released:
+    // on failure, a fault of the kernel that writes the records among them, the
+    // context keeps its previous opacity source unchanged, and work on any
+    // stream the context is given later finds the records written
     float *tab = nullptr;
     hipError_t e = device_alloc(reinterpret_cast<void **>(&tab), (off + 8 * ncell) * sizeof(float));
     if (e != hipSuccess) return fail(M1_ENOMEM, "m1_set_opacity_table: allocation failed");
@@ -543,6 +545,7 @@ m1_status m1_set_opacity_table(m1_ctx *c, int nr, int nt, double lr0, double lr1
                            nt, tab + off);
         e = hipGetLastError();
     }
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         hipFree(tab);
         return hip_fail(e, "m1_set_opacity_table: upload");
