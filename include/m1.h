@@ -383,8 +383,12 @@ m1_status m1_step_rk2(m1_ctx *ctx, double dt);
 
 /* Device pointers of the library's transported state E*, Fx*, Fy*, Fz*
  * (the state between the explicit and the implicit part of the Sect. 2.4
- * step list; valid after m1_step_explicit; owned by the library;
- * m1_step_rk2 may not store it).  Gray states only (M1_ENOTSUP with groups). */
+ * step list; valid after m1_step_explicit; owned by the library).  Gray
+ * states only (M1_ENOTSUP with groups).  M1_ESTATE after a step of
+ * m1_step_rk2 that took its stages in one kernel each (constant, power-law
+ * and tabulated opacities, most grids) and stored no transported state, until
+ * the next m1_step_explicit; where that step runs split (network opacities,
+ * among others) the arrays hold the second stage's. */
 m1_status m1_transported(m1_ctx *ctx, void **E, void **Fx, void **Fy, void **Fz);
 
 /* Re-evaluate the opacity cache (rho kappa_P and the optical depth of the

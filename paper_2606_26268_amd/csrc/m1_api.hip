@@ -468,6 +468,7 @@ m1_status m1_bind_state(m1_ctx *c, const m1_fields *f) try
     c->f = *f;
     c->bound = true;
     c->transported = false;
+    c->star_lost = false;
     e = hipMemsetAsync(c->cnt, 0, CNT_BYTES, c->stream);
     if (e == hipSuccess) e = launch_opacity_init(c);
     if (e != hipSuccess) {
@@ -730,6 +731,7 @@ m1_status m1_step_explicit(m1_ctx *c, double dt)
     hipError_t e = launch_transport(c, dt);
     if (e != hipSuccess) return hip_fail(e, "m1_step_explicit launch");
     c->transported = true;
+    c->star_lost = false;
     return M1_OK;
 }
 
@@ -835,10 +837,12 @@ m1_status m1_step_rk2(m1_ctx *c, double dt)
     // cache following each stage's written state
     // each stage's transport and implicit step in one kernel where that serves
     if (fused_stages(c)) {
+        // the transported fields are not stored, the first holds optical depths
+        c->star_lost = true;
+        c->transported = false;
         hipError_t e = launch_stage(c, dt, 1);
         if (e == hipSuccess) e = launch_stage(c, dt, 2);
         if (e != hipSuccess) return hip_fail(e, "m1_step_rk2 stage");
-        c->transported = false;
         return M1_OK;
     }
     unsigned char *sv = static_cast<unsigned char *>(c->rk2_save);
@@ -849,6 +853,7 @@ m1_status m1_step_rk2(m1_ctx *c, double dt)
     if (e == hipSuccess) e = launch_implicit_rk2(c, dt, 2);
     if (e != hipSuccess) return hip_fail(e, "m1_step_rk2 stage");
     c->transported = false;
+    c->star_lost = false;
     return M1_OK;
 }
 
@@ -857,6 +862,8 @@ m1_status m1_transported(m1_ctx *c, void **E, void **Fx, void **Fy, void **Fz)
     if (!c || !E || !Fx || !Fy || !Fz) return fail(M1_EINVAL, "m1_transported: NULL argument");
     if (!c->bound) return fail(M1_ESTATE, "m1_transported: no state bound");
     if (c->grp.m > 1) return fail(M1_ENOTSUP, "m1_transported: gray states only");
+    if (c->star_lost)
+        return fail(M1_ESTATE, "m1_transported: m1_step_rk2 did not store its transported states; call m1_step_explicit");
     *E = c->star[0];
     *Fx = c->star[1];
     *Fy = c->star[2];

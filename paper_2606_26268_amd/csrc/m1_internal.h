@@ -167,6 +167,7 @@ struct m1_ctx {
     double *partials = nullptr;            // reduction scratch
     int npartial = 0;
     bool transported = false;
+    bool star_lost = false;                // star holds no transported state: the last step's stages were fused
     void *rk2_save = nullptr;              // first-stage state U1 of m1_step_rk2
     size_t rk2_rad_bytes = 0;              // its per-field radiation stride (all groups)
 
