@@ -329,9 +329,11 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     // Slopes, x slots then y slots (LimO3: upper-face slopes).  The x fluxes
     // take the place of the x slopes: the face left of column c is computed by
     // the wavefront that owns its row, which has read every slope of the row
-    // but the last two by then, and goes to the slot of column c - 1; the face
+    // but the last two by then (a wave barrier stands between its reads and its
+    // stores), and goes to the slot of column c - 1; the face
     // right of the last column reads the last two slots and goes to the last,
     // which only it reads.
+    static_assert(64 % TX == 0, "a row's faces belong to one wavefront");
     __shared__ R ss[4][NXS + NYS];
     __shared__ R ssl[LIMO3 ? 4 : 1][LIMO3 ? NXS + NYS : 1];   // LimO3: lower-face slopes
     __shared__ R sfy[4][TY + 1][TX];
@@ -639,6 +641,13 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
             }
             face_flux_s<R>(p == 2 ? int(y) : p, qb, qc, slb, slc, centre(b), centre(b + qst), hp, hm,
                            depth(b) + depth(b + qst), fl, recon, riemann);
+            // a lane's x flux takes the slot its left neighbour read as slc
+            // (with LimO3 slc is in an array of its own): every lane's reads
+            // come before any lane's stores
+            if (p == 0 && !LIMO3) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
             R *dst = y ? &sfy[0][0][0] : &ss[0][0];
             const int fs = y ? (TY + 1) * TX : NXS + NYS;
 #pragma unroll
