@@ -11,6 +11,7 @@
 // small layers on the vector ALU.  Per-block gradients go to a partial buffer
 // that one kernel reduces in a fixed order before the Adam update (Kingma &
 // Ba 2015), so training is deterministic.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -752,16 +753,24 @@ int mlp_gradient(m1_ctx *c, const float *samples, long n, const float *theta, fl
     ta.pk = c->mlp_dev;
     ta.samples = samples;
     ta.n_train = n;
-    ta.offset = 0;
     ta.inv_batch = 1.0f / float(n);
     ta.op = c->op;
-    ta.partial = partial;
-    ta.loss_part = loss_part;
-    hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(nblk), dim3(TRAIN_THREADS), 0, c->stream, ta);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(RED_BLOCKS + 1), dim3(256), 0, c->stream, partial, nblk,
-                       loss_part, g, L);
+    // a launch takes fewer than 2^32 threads: 2^22 blocks at a time
+    constexpr int BLOCKS = 1 << 22;
+    hipError_t e = hipSuccess;
+    for (int b = 0; b < nblk && e == hipSuccess; b += BLOCKS) {
+        ta.offset = 64L * b;
+        ta.partial = partial + size_t(b) * NP;
+        ta.loss_part = loss_part + b;
+        hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(std::min(BLOCKS, nblk - b)), dim3(TRAIN_THREADS), 0, c->stream, ta);
+        e = hipGetLastError();
+    }
     float Lh = 0.f;
-    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_mlp_reduce, dim3(RED_BLOCKS + 1), dim3(256), 0, c->stream, partial, nblk,
+                           loss_part, g, L);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipMemcpyAsync(grad, g, NP * sizeof(float), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&Lh, L, sizeof(float), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
