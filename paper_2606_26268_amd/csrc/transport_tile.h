@@ -101,23 +101,39 @@ template <int GEOM, int D>
 constexpr bool same_area = GEOM == M1_CARTESIAN || (GEOM == M1_CYLINDRICAL && D > 0) ||
                            (GEOM == M1_SPHERICAL && D == 2);
 
-// A_hi/V Phi_hi - A_lo/V Phi_lo of one direction.  With equal area factors
-// it is formed as a (Phi_hi - Phi_lo), so that equal face fluxes (a uniform
-// state) cancel exactly: the contracted a Phi_hi - a Phi_lo would leave the
-// rounding error of one product behind in every cell.
-template <bool SAME, typename R>
-__device__ __forceinline__ R face_diff(R al, R ah, R flo, R fhi)
+// A_hi/V Phi_hi - A_lo/V Phi_lo of one direction, from the lower area factor and the
+// difference of the two, da.  Equal face fluxes of equal areas (a uniform state)
+// cancel exactly: the contracted a Phi_hi - a Phi_lo would leave the
+// rounding error of one product behind in every cell.  Where the areas differ, da is
+// the factor of the geometric sources (area_step), and the pressure on the
+// wider face meets its source in the same factor: with
+// a_hi Phi_hi - a_lo Phi_lo the roundings of two area factors, each times dt c_hat,
+// are left behind, many times da P on a grid of thin rings or shells.  (An isotropic
+// field at rest on 3000 rings between R = 1 and 2 moved by up to 6000 u da E in a step,
+// by 3500 with dt c_hat applied after the difference, and by less than 5 so; u is the unit
+// roundoff.)
+template <int GEOM, int D, typename R>
+__device__ __forceinline__ R face_diff(R al, R da, R flo, R fhi)
 {
-    if constexpr (SAME)
-        return ah * (fhi - flo);
-    else
-        return ah * fhi - al * flo;
+    const R d = al * (fhi - flo);
+    return same_area<GEOM, D> ? d : d + da * fhi;
+}
+
+// A_hi/V - A_lo/V of a cell (times dt c_hat, as tr1): radial (b - a) / ring on the
+// cylindrical and (b^2 - a^2) / shell on the spherical grid, once and twice the radius
+// factor tr1 of the other directions; polar cot(theta)_eff times it.
+template <int GEOM, int D, typename R>
+__device__ __forceinline__ R area_step(R tr1, R ct)
+{
+    if (same_area<GEOM, D>) return R(0);
+    return D == 1 ? ct * tr1 : (GEOM == M1_SPHERICAL ? tr1 + tr1 : tr1);
 }
 
 // Contribution of direction D to the flux divergence of the cell at index t
 // along D (row base `base`, stride `stride`): reconstruct cells t-1, t, t+1
 // (stencil t-2 .. t+2), take HLL fluxes at both faces of cell t and add
-// A_hi/V * Phi_hi - A_lo/V * Phi_lo to acc.
+// A_hi/V * Phi_hi - A_lo/V * Phi_lo to acc (tr: dt c_hat times the direction's
+// factors of the other coordinates).
 template <typename R, int D, int GEOM>
 __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int stride, int t,
                                               R tr, Centre<R> c0, R acc[4])
@@ -152,9 +168,10 @@ __device__ __forceinline__ void direction_div(const TArgs<R> &a, int base, int s
     R flo[4], fhi[4];
     face_flux_s<R>(D, q[1], q[2], sm, slo, cm, c0, hp[t + 1], hm[t + 2], tm + t0, flo, a.recon, a.riemann);
     face_flux_s<R>(D, q[2], q[3], shi, sp, c0, cp, hp[t + 2], hm[t + 3], t0 + tp, fhi, a.recon, a.riemann);
-    const R al = a.m.alo[D][t] * tr, ah = a.m.ahi[D][t] * tr;   // tr carries dt c_hat
+    const R al = a.m.alo[D][t] * tr;                     // tr carries dt c_hat
+    const R da = area_step<GEOM, D>(D == 0 ? a.m.inv_reff[t] * tr : tr, GEOM == M1_SPHERICAL && D == 1 ? a.m.cot_eff[t] : R(0));
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] += face_diff<same_area<GEOM, D>>(al, ah, flo[v], fhi[v]);
+    for (int v = 0; v < 4; ++v) acc[v] += face_diff<GEOM, D>(al, da, flo[v], fhi[v]);
 }
 
 template <typename R, int D>
@@ -340,7 +357,7 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
     // spacing ratio and the two centre-to-face offsets of the cells of columns
     // -1 .. TX and rows -1 .. TY
     __shared__ R smx[3][TX + 2], smy[3][TY + 2];
-    __shared__ R sux[3][TX], suy[GEOM == M1_SPHERICAL ? 4 : 2][TY];
+    __shared__ R sux[2][TX], suy[GEOM == M1_SPHERICAL ? 3 : 1][TY];
     R *const sqf = &sq[0][0][0];
     // of the cell at flat index b of sq
     const auto depth = [&](int b) { return (&st[0][0])[b - HX]; };
@@ -422,24 +439,22 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         smy[1][q] = m <= n1 ? a.m.hp[1][m + 2] : R(0);
         smy[2][q] = m <= n1 ? a.m.hm[1][m + 2] : R(0);
     }
-    // Update factors of the tile's columns (the area factors of x, dt c_hat
-    // among them, and the radius factor of the other directions, which is also
-    // that of the geometric sources) and rows (the area factors of y, the sine
-    // factor of z and cot theta).
+    // Update factors of the tile's columns (the lower area factor of x, dt c_hat
+    // in it, and the radius factor of the other directions, which is also
+    // that of the geometric sources) and rows (the lower area factor of y, the
+    // sine factor of z and cot theta); the upper faces' follow (area_step).
     if (tid >= 128 && tid < 128 + TX) {
         const int c = tid - 128, m = x0 + c;
         const R dtc = m < n0 ? a.dt * a.c_hat : R(0);
         const int mm = min(m, n0 - 1);
         sux[0][c] = a.m.alo[0][mm] * dtc;
-        sux[1][c] = a.m.ahi[0][mm] * dtc;
-        sux[2][c] = a.m.trA[1][mm] * dtc;
+        sux[1][c] = a.m.trA[1][mm] * dtc;
     } else if (tid >= 192 && tid < 192 + TY) {
         const int q = tid - 192, mm = min(y0 + q, n1 - 1);
         suy[0][q] = a.m.alo[1][mm];
-        suy[1][q] = a.m.ahi[1][mm];
         if (GEOM == M1_SPHERICAL) {
-            suy[2][q] = a.m.trB[2][mm];
-            suy[3][q] = a.m.cot_eff[mm];
+            suy[1][q] = a.m.trB[2][mm];
+            suy[2][q] = a.m.cot_eff[mm];
         }
     }
     const R dtc = a.dt * a.c_hat;
@@ -672,18 +687,18 @@ __device__ __forceinline__ void transport_tile(const TArgs<R> &a, int nz_chunk, 
         if (live) {
             R acc[4], Us[4];
             const int xr = xs + 1 + (lx == TX - 1);      // slot of the flux right of the cell
-            const R axl = sux[0][lx], axh = same_area<GEOM, 0> ? axl : sux[1][lx];
-            const R tr1 = GEOM == M1_CARTESIAN ? dtc : sux[2][lx];
-            const R ayl = suy[0][ly] * tr1, ayh = same_area<GEOM, 1> ? ayl : suy[1][ly] * tr1;
-            const R tr2 = GEOM == M1_SPHERICAL ? suy[2][ly] * tr1 : dtc;
+            const R axl = sux[0][lx];
+            const R tr1 = GEOM == M1_CARTESIAN ? dtc : sux[1][lx];
+            const R ayl = suy[0][ly] * tr1;
+            const R tr2 = GEOM == M1_SPHERICAL ? suy[1][ly] * tr1 : dtc;
             const R azl = NDIM == 3 ? a.m.alo[2][k] * tr2 : R(0);
-            const R azh = NDIM == 2 || same_area<GEOM, 2> ? azl : a.m.ahi[2][k] * tr2;
-            const R ct = GEOM == M1_SPHERICAL ? suy[3][ly] : R(0);
+            const R ct = GEOM == M1_SPHERICAL ? suy[2][ly] : R(0);
+            const R dax = area_step<GEOM, 0>(tr1, ct), day = area_step<GEOM, 1>(tr1, ct);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                acc[v] = face_diff<same_area<GEOM, 0>>(axl, axh, ss[v][xs], ss[v][xr]) +
-                         face_diff<same_area<GEOM, 1>>(ayl, ayh, sfy[v][ly][lx], sfy[v][ly + 1][lx]) +
-                         (NDIM == 3 ? face_diff<same_area<GEOM, 2>>(azl, azh, Fa[v], Fb[v]) : R(0));
+                acc[v] = face_diff<GEOM, 0>(axl, dax, ss[v][xs], ss[v][xr]) +
+                         face_diff<GEOM, 1>(ayl, day, sfy[v][ly][lx], sfy[v][ly + 1][lx]) +
+                         (NDIM == 3 ? face_diff<GEOM, 2>(azl, R(0), Fa[v], Fb[v]) : R(0));
             if (NDIM == 2 && a.ign[2]) ignorable_div<R, 2>(a, Wa, Ca, tr2, acc);
             finish_cell<R, GEOM>(a, Wa, Ca, acc, tr1, ct, Us);
             fin(in, Us, Ta, i, j, k, base, cell);
