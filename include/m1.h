@@ -115,8 +115,10 @@ typedef struct {
  * stream_reads  how the implicit step reads its inputs (each once per
  *         step): M1_STREAM_AUTO (default) with a nontemporal hint, which
  *         streams them past the caches and leaves the last-level cache to
- *         the step's outputs, when a step moves at least 384 MiB, else as
- *         plain loads; M1_STREAM_ON always; M1_STREAM_OFF never.  Results are
+ *         the step's outputs, when a step moves at least 384 MiB, else (and
+ *         in second-order stages that take transport and sources in one
+ *         kernel) as plain loads; M1_STREAM_ON always; M1_STREAM_OFF never.
+ *         Results are
  *         bit-identical; only the speed differs (execution tuning, no
  *         passage of the paper). */
 typedef enum { M1_STREAM_AUTO = 0, M1_STREAM_ON = 1, M1_STREAM_OFF = 2 } m1_stream_reads;

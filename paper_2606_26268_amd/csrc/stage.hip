@@ -153,9 +153,14 @@ static hipError_t launch_s(m1_ctx *c, double dt, const Metric<R> &met, int stage
     const size_t per = c->rk2_rad_bytes;
     const void *const u1[4] = {sv, sv + per, sv + 2 * per, sv + 3 * per};
     fill_targs(c, a.t, met, dt, stage == 1 ? nullptr : u1, tau_in);
-    const double N = double(c->n[0]) * c->n[1] * c->n[2];
     a.cus = c->cus;
-    a.nt = stream_reads(c, N * (8.0 * sizeof(R) + 72.0 + (con ? 0.0 : 4.0 * sizeof(R))));
+    // A stage's own inputs (the gas and the opacity cache) are streamed past the caches only
+    // where the caller asks for it: its reads wait behind issue, not behind
+    // memory.  A step with streaming reads and without: 128^3 118.0 and 117.2 us,
+    // 192^3 510.6 and 510.7, 256^3 1060 and 1047 (FP32, constant opacities);
+    // 160x144x128 323.8 and 322.7, 192^3 737 and 739 (FP64); 192x96x192 290 and
+    // 289, 256x192x192 750 and 741 (FP32, table).
+    a.nt = c->par.stream_reads == M1_STREAM_ON;
 #define M1_STAGE(G)                                  \
     if (con) launch_geom<R, G, true>(c, a);           \
     else launch_geom<R, G, false>(c, a)
