@@ -717,6 +717,9 @@ int mlp_train(m1_ctx *c, const m1_train_cfg *cfg, m1_train_report *rep)
     hipEventDestroy(ev1);
     hipFree(buf);
     if (e != hipSuccess) {
+        // the packed network is part-trained by now: the one in use before, if
+        // any, goes back
+        if (!c->mlp_theta.empty()) mlp_pack(c, std::vector<float>(c->mlp_theta).data(), c->op.norm);
         set_error(std::string("m1_mlp_train: ") + hipGetErrorString(e));
         return int(M1_EDEVICE);
     }
