@@ -6,7 +6,8 @@
 // to the library's buffer, the average to the bound arrays while the second
 // transport reads U1), so the implicit step can take the transported cell from
 // registers: the four transported fields are neither written nor read back
-// (64 of 245 bytes a cell and step in FP32, 128 of 325 in FP64), and the
+// (64 of 328 bytes a cell and step in FP32, 128 of 480 in FP64, with constant
+// opacities), and the
 // implicit step's loads overlap the transport's arithmetic.  Where opacities
 // depend on temperature a stage writes the optical depths of its new state to
 // another array than the one neighbouring cells still read: stage 1 to the
@@ -15,11 +16,11 @@
 // What bounds it: vector issue in 3D (transport and solve are about 800 FP32
 // operations a cell and stage), where the split step alternated between an
 // issue-bound and a memory-bound kernel.  A second-order step, split -> fused:
-// 256^3 FP32 1363 -> 1024 us, 128^3 FP32 166 -> 113 us and FP64 304 -> 220 us,
-// 192x96x192 FP32 298 -> 240 us (constant opacities) and 310 -> 286 us (table),
-// 128^3 FP32 power law 185 -> 151 us, 1D 2000 cells 17.3 -> 13.8 us, 2D 1000^2 FP64
-// 187 -> 153 us and in tiles 88 us, 300x200 shell with the table, FP32, 24.0 ->
-// 19.8 and in tiles 16.0 us, 300^2 beam with LimO3 in FP64 38 -> 33 -> 25.7 us.
+// 256^3 FP32 1363 -> 1025 us, 128^3 FP32 166 -> 114 us and FP64 304 -> 220 us,
+// 192x96x192 FP32 298 -> 241 us (constant opacities) and 310 -> 289 us (table),
+// 128^3 FP32 power law 185 -> 147 us, 1D 2000 cells FP64 17.3 -> 13.3 us, 2D 1000^2 FP64
+// 187 -> 153 us and in tiles 92 us, 300x200 shell with the table, FP32, 24.0 ->
+// 19.8 and in tiles 16.7 us, 300^2 beam with LimO3 in FP64 38 -> 33 -> 24.8 us.
 //
 // Covers gray states with constant, power-law and tabulated opacities, in 1D
 // and 2D with every variant, in 3D with the default scheme and, in FP64 with
@@ -173,13 +174,14 @@ static hipError_t launch_s(m1_ctx *c, double dt, const Metric<R> &met, int stage
     return hipGetLastError();
 }
 
-// Temperature-dependent opacities in 3D in FP64: the logarithms, powers and
-// exponentials (about 250 FP64 operations a cell) hide behind memory in the
-// split implicit kernel and add to the issue-bound fused one, about 5 us per
-// million cells and stage (128^3 power law: split 324 us, fused 334;
-// 192x96x192 table: 538 and 574), against some 2.2 us a stage for the launch
-// the fused stage saves (154,000 cells, power law: split 51.4, fused 47.8): the
-// sides meet near half a million cells.
+// Temperature-dependent opacities in 3D in FP64 step split above half a million
+// cells.  The line was drawn with the fused kernel at two waves per SIMD, where the
+// logarithms, powers and exponentials (about 250 FP64 operations a cell) cost more
+// than the transported state's way through memory.  At today's three waves the
+// fused stages are shorter on either side of it (split, fused: 154,000 cells, power
+// law, 53.7 and 47.2 us; 885,000 151.6 and 132.7; 128^3 330 and 296; 192x96x192
+// with the table 536 and 486); the split step stays above it because it stores the
+// transported state, which m1_transported then answers.
 constexpr long FUSED_P64_CELLS = 1L << 19;
 
 bool fused_stages(const m1_ctx *c)

@@ -54,13 +54,13 @@ __global__ void __launch_bounds__((Tile<TYB>::NT),
     transport_tile<R, 3, GEOM, GENERAL, TYB, LIMO3>(a, nz_chunk, tiles_x, tiles_y, nblocks, cus, StoreCell<R>{a.out, a.out_fs});
 }
 
-// 2D: one 32 x 8 tile a block.  What bounds it: FP32 memory (1000^2 cells:
-// 18.4 us, 36 bytes a cell at 2.0 TB/s; a large copy takes 7.5 us for them) and
-// the chain load - slopes - faces - update behind three barriers, with six blocks
-// on a compute unit to overlap them; FP64 issue and that chain, three blocks on a
-// unit (52.6 KB of LDS each).  Against a thread per cell, which computed every
+// 2D: one 32 x 8 tile a block.  What bounds it: the chain load - slopes - faces -
+// update behind three barriers, which the six FP32 blocks on a compute unit overlap in
+// part (1000^2 cells: 18-20 us, where a large copy takes 7.5 us for their 36 bytes a
+// cell); in FP64 that chain and issue, three blocks on a unit (52.6 KB of LDS
+// each).  Against a thread per cell, which computed every
 // face twice and every slope three times: 1000^2 cells FP32 30.3 -> 18.4 us, FP64
-// 66.6 -> 37.9 us, LimO3 FP32 33.1 -> 25.9 us; 300 x 200 FP32 6.1 -> 5.3 us, FP64
+// 66.6 -> 38 us, LimO3 FP32 33.1 -> 25.9 us; 300 x 200 FP32 6.1 -> 5.3 us, FP64
 // 7.8 -> 6.3 us.
 template <typename R, int GEOM, bool GENERAL, bool LIMO3>
 __global__ void __launch_bounds__(256, (sizeof(R) == 4 ? 4 : (LIMO3 ? 2 : 3)))
