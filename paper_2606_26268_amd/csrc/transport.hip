@@ -24,9 +24,9 @@ __global__ void __launch_bounds__(256) k_transport(TArgs<R> a)
 // direction, one for its lower and one for its upper face, and takes the
 // 32 x 8 tile in FP64 (the 512-thread block spilled).
 //
-// What bounds it: vector issue, in FP32 (about 620 instructions a cell, 57 of
-// them transcendental at two slots and a third; 78 % of the cycles issue on the
-// 192x96x192 grid, the rest is ramp, tail and barriers) and in FP64 (about 950,
+// What bounds it: vector issue, in FP32 (about 640 instructions a cell, 57 of
+// them transcendental at two slots and a third; 80 % of the cycles issue on the
+// 192x96x192 grid, the rest is ramp, tail and barriers) and in FP64 (about 970,
 // 69 % of the cycles).  A step of the 128^3 box went from 99 to 92.9 us (FP32) and
 // 176 to 153.8 us (FP64) with the closure without 1 / |F|^2, the face fix on
 // f^2 and the regrouped Riemann flux of m1_device.h, on to 88.5 and 143.5 us
