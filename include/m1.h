@@ -118,9 +118,8 @@ typedef struct {
  *         the step's outputs, when a step moves at least 384 MiB, else (and
  *         in second-order stages that take transport and sources in one
  *         kernel) as plain loads; M1_STREAM_ON always; M1_STREAM_OFF never.
- *         Results are
- *         bit-identical; only the speed differs (execution tuning, no
- *         passage of the paper). */
+ *         Results are bit-identical; only the speed differs (execution
+ *         tuning, no passage of the paper). */
 typedef enum { M1_STREAM_AUTO = 0, M1_STREAM_ON = 1, M1_STREAM_OFF = 2 } m1_stream_reads;
 typedef struct {
     double c;
@@ -268,7 +267,8 @@ m1_status m1_set_opacity_mlp(m1_ctx *ctx, const m1_mlp *w);
 /* Train the surrogate on the GPU (see m1_train_cfg) against the bound
  * table (Sect. 3.7 tabulated opacities; the surrogate itself is an
  * addition, see m1_set_opacity_mlp); on success the trained network
- * becomes the context's opacity source.  Synchronous. */
+ * becomes the context's opacity source, on failure the network in use stays.
+ * Synchronous. */
 m1_status m1_mlp_train(m1_ctx *ctx, const m1_train_cfg *cfg, m1_train_report *rep);
 
 /* Copy the current network parameters to host theta (M1_MLP_NPARAM floats)
